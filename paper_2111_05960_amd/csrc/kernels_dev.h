@@ -398,9 +398,9 @@ __device__ __forceinline__ void bstore16_nt(uint16_t v, __amdgpu_buffer_rsrc_t r
   __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(V, v), r, voff, soff, 2);
 }
 
-template <int TX, int TY, int ZC, class Codec, class LG, class LH, bool kGen, bool kWalls>
+template <int TX, int TY, class Codec, class LG, class LH, bool kGen, bool kWalls>
 __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
-    k_dev_fused3d(Geo g, Coef<float> Kin, DevStep b, int tiles_x, int tiles_xy, int ntiles) {
+    k_dev_fused3d(Geo g, Coef<float> Kin, DevStep b, int tiles_x, int tiles_xy, int ntiles, int zc) {
   const Coef<float> K = variant<kGen>(Kin);
   using Shape = TileShape<TX, TY>;
   constexpr int Q = LG::Q;  // g lattice (D3Q19 or D3Q7)
@@ -443,7 +443,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
   for (int tile = first_tile(); tile < ntiles; tile += gridDim.x) {
   const int chunk = tile / tiles_xy, txy = tile % tiles_xy;
   const int X0 = tile_column(txy, tiles_x, chunk, kWalls) * TX, Y0 = (txy / tiles_x) * TY;
-  const int z0 = chunk * ZC, z1 = min(z0 + ZC, nz);
+  const int z0 = chunk * zc, z1 = min(z0 + zc, nz);
   const int ux = X0 - 1 + tx, uy = Y0 - 1 + ty;
   const bool out = valid && ux < nx && uy < ny && tx >= 1 && tx <= TX && ty >= 1 && ty <= TY;
   // region nodes beyond a wall take no part (with walls only)
@@ -817,16 +817,17 @@ struct DevFused3D {
     // walls (64 x 9 tiles: 7296 at 512^3, 28.5 passes, against 14.25 with 64)
     constexpr int TX = 64, TY = kWalls ? GPLBM_DEV_WALL_TY : GPLBM_DEV_TY, ZC = kWalls ? 32 : 128;
     constexpr int NT = TileShape<TX, TY>::NT;
-    auto kernel = k_dev_fused3d<TX, TY, ZC, Codec, LG, LH, kGen, kWalls>;
+    auto kernel = k_dev_fused3d<TX, TY, Codec, LG, LH, kGen, kWalls>;
     const int tiles_x = (g.nx + TX - 1) / TX;
     const int tiles_y = (g.ny + TY - 1) / TY;
-    const int chunks = (g.nz + ZC - 1) / ZC;
     const int tiles_xy = tiles_x * tiles_y;
-    const int ntiles = tiles_xy * chunks;
     static int resident[64] = {0};
-    const int grid = resident_grid(kernel, NT, ntiles, resident);
-    if (grid <= 0) return -1;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), 0, st, g, K, b, tiles_x, tiles_xy, ntiles);
+    const int slots = resident_slots(kernel, NT, resident);
+    if (slots <= 0) return -1;
+    const int zc = chunk_planes(tiles_xy, g.nz, ZC, slots);
+    const int ntiles = tiles_xy * ((g.nz + zc - 1) / zc);
+    hipLaunchKernelGGL(kernel, dim3(resident_grid(slots, ntiles)), dim3(NT), 0, st, g, K, b, tiles_x,
+                       tiles_xy, ntiles, zc);
     return 0;
   }
   static int launch(const Geo& g, const Coef<float>& K, const DevStep& b, hipStream_t st) {
@@ -1040,9 +1041,9 @@ struct DevFused2D {
     const int tiles_y = (g.ny + TY - 1) / TY;
     const int ntiles = tiles_x * tiles_y;
     static int resident[64] = {0};
-    const int grid = resident_grid(kernel, NT, ntiles, resident);
-    if (grid <= 0) return -1;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), 0, st, g, K, b, tiles_x, ntiles);
+    const int slots = resident_slots(kernel, NT, resident);
+    if (slots <= 0) return -1;
+    hipLaunchKernelGGL(kernel, dim3(resident_grid(slots, ntiles)), dim3(NT), 0, st, g, K, b, tiles_x, ntiles);
     return 0;
   }
 };

@@ -164,9 +164,6 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT), (sizeof(S) == 4 ? 6 :
 #ifndef GPLBM_F2_TY
 #define GPLBM_F2_TY 8
 #endif
-#ifndef GPLBM_F2_PERSIST
-#define GPLBM_F2_PERSIST 1
-#endif
 
 inline bool fused2d_supported(int, int) { return true; }
 
@@ -180,13 +177,9 @@ struct Fused2D {
     const int tiles_y = (g.ny + TY - 1) / TY;
     const int ntiles = tiles_x * tiles_y;
     static int resident[64] = {0};
-#if GPLBM_F2_PERSIST
-    const int grid = resident_grid(kernel, NT, ntiles, resident);
-#else
-    const int grid = (ntiles + kNumXcd - 1) / kNumXcd * kNumXcd;
-#endif
-    if (grid <= 0) return -1;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), 0, st, g, K, b, tiles_x, ntiles);
+    const int slots = resident_slots(kernel, NT, resident);
+    if (slots <= 0) return -1;
+    hipLaunchKernelGGL(kernel, dim3(resident_grid(slots, ntiles)), dim3(NT), 0, st, g, K, b, tiles_x, ntiles);
     return 0;
   }
 };

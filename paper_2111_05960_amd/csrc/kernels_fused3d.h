@@ -175,10 +175,10 @@ struct Fused3DConfig<D3Q7, float> {
   static constexpr bool prefetch = false;
 };
 
-template <int TX, int TY, int ZC, Carry kCarryMode, bool kPrefetch, class L, class LH, class S,
-          class C, bool kGen, bool kWalls>
+template <int TX, int TY, Carry kCarryMode, bool kPrefetch, class L, class LH, class S, class C,
+          bool kGen, bool kWalls>
 __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
-    k_fused3d(Geo g, Coef<C> Kin, StepBufs<S> b, int tiles_x, int tiles_xy, int ntiles) {
+    k_fused3d(Geo g, Coef<C> Kin, StepBufs<S> b, int tiles_x, int tiles_xy, int ntiles, int zc) {
   const Coef<C> K = variant<kGen>(Kin);
   using Shape = TileShape<TX, TY>;
   constexpr int Q = L::Q, QH = LH::Q;
@@ -227,7 +227,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
   for (int tile = first_tile(); tile < ntiles; tile += gridDim.x) {
     const int chunk = tile / tiles_xy, txy = tile % tiles_xy;
     const int X0 = tile_column(txy, tiles_x, chunk, kWalls) * TX, Y0 = (txy / tiles_x) * TY;
-    const int z0 = chunk * ZC, z1 = min(z0 + ZC, nz);
+    const int z0 = chunk * zc, z1 = min(z0 + zc, nz);
 
     const int ux = X0 - 1 + tx, uy = Y0 - 1 + ty;
     const bool out = valid && ux < nx && uy < ny && tx >= 1 && tx <= TX && ty >= 1 && ty <= TY;
@@ -628,16 +628,17 @@ struct Fused3D {
   static int run(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {
     constexpr int TX = Cfg::TX, TY = Cfg::TY, ZC = Cfg::ZC;
     constexpr int NT = TileShape<TX, TY>::NT;
-    auto kernel = k_fused3d<TX, TY, ZC, Cfg::carry, Cfg::prefetch, L, LH, S, C, kGen, kWalls>;
+    auto kernel = k_fused3d<TX, TY, Cfg::carry, Cfg::prefetch, L, LH, S, C, kGen, kWalls>;
     const int tiles_x = (g.nx + TX - 1) / TX;
     const int tiles_y = (g.ny + TY - 1) / TY;
-    const int chunks = (g.nz + ZC - 1) / ZC;
     const int tiles_xy = tiles_x * tiles_y;
-    const int ntiles = tiles_xy * chunks;
     static int resident[64] = {0};
-    const int grid = resident_grid(kernel, NT, ntiles, resident);
-    if (grid <= 0) return -1;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), 0, st, g, K, b, tiles_x, tiles_xy, ntiles);
+    const int slots = resident_slots(kernel, NT, resident);
+    if (slots <= 0) return -1;
+    const int zc = chunk_planes(tiles_xy, g.nz, ZC, slots);
+    const int ntiles = tiles_xy * ((g.nz + zc - 1) / zc);
+    hipLaunchKernelGGL(kernel, dim3(resident_grid(slots, ntiles)), dim3(NT), 0, st, g, K, b, tiles_x,
+                       tiles_xy, ntiles, zc);
     return 0;
   }
   static int launch(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {

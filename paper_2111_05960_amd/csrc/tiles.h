@@ -16,6 +16,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace gplbm {
 
 constexpr int kNumXcd = 8;
@@ -51,10 +53,10 @@ struct TileShape {
   }
 };
 
-// Resident grid of a persistent kernel: blocks per CU x CUs, a multiple of
-// the XCD count, no more than the tiles need.  Cached per device in cache[].
+// Resident slots of a persistent kernel: blocks per CU x CUs, a multiple of
+// the XCD count.  Cached per device in cache[].  -1 on an error.
 template <class Kern>
-inline int resident_grid(Kern kernel, int threads, int ntiles, int* cache) {
+inline int resident_slots(Kern kernel, int threads, int* cache) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return -1;
   if (cache[dev] == 0) {
@@ -65,7 +67,38 @@ inline int resident_grid(Kern kernel, int threads, int ntiles, int* cache) {
       return -1;
     cache[dev] = max(kNumXcd, (per_cu * cus) / kNumXcd * kNumXcd);
   }
-  return min(cache[dev], (ntiles + kNumXcd - 1) / kNumXcd * kNumXcd);
+  return cache[dev];
+}
+
+// Grid of a persistent kernel: no more blocks than the tiles need, a multiple
+// of the XCD count.
+inline int resident_grid(int slots, int ntiles) {
+  return min(slots, (ntiles + kNumXcd - 1) / kNumXcd * kNumXcd);
+}
+
+// Planes per z chunk of a z-marching kernel, at most zmax (the length measured
+// best on 512^3, where every slot has many tiles).  A pass over the resident
+// blocks costs its zc planes, the two halo planes and about one plane of
+// filling the rings, and the time of a plane hardly depends on how many of
+// the blocks run (FP32, FP16 deviations 10.1-12.8 us, FP64 9.0-13.8 us
+// between 20 and 256 blocks on 256 CUs), so the step takes passes x (zc + 3)
+// planes: the chunk is the longest that fits the tiles into the passes of
+// least cost.  64^3 FP64 314 -> 56 us, FP32 walls 287 -> 41 us, FP16 601 ->
+// 38 us; 128^3 FP16 1208 -> 142 us; 256^3 FP16 1251 -> 953 us.  More than
+// four passes above the fewest never won.
+inline int chunk_planes(int tiles_xy, int nz, int zmax, int slots) {
+  zmax = min(zmax, nz);
+  const int64_t fewest = (int64_t)tiles_xy * ((nz + zmax - 1) / zmax);
+  const int64_t p0 = (fewest + slots - 1) / slots;
+  int best = zmax;
+  int64_t cost = p0 * (zmax + 3);
+  for (int64_t p = p0; p < p0 + 4; ++p) {
+    const int64_t chunks = min(p * slots / tiles_xy, (int64_t)nz);
+    if (chunks < 1) continue;
+    const int zc = int((nz + chunks - 1) / chunks);
+    if (zc <= zmax && p * (zc + 3) < cost) best = zc, cost = p * (zc + 3);
+  }
+  return best;
 }
 
 // First tile of this block in the first pass (the slots of an XCD take
