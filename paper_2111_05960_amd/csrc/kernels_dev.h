@@ -849,12 +849,12 @@ struct DevFused3D {
 //     wall), then runs the g collision of step n+1.
 // The values and the order of every sum are those of the split kernels, so
 // the two schedules give identical bits.
-template <class P>
-struct LatticeTag {
-  using type = P;
-};
-
-template <int TX, int TY, class Codec, class L, class LH, bool kGen>
+// Bound by instruction issue and load latency: one batch of loads with
+// selected addresses in place of a branch and a 64-bit address computation per
+// population, and two blocks of 8 rows per CU (68 VGPRs) in place of one of 13
+// (114): 512^2 FP16 23.9 -> 10.5 us, 1024^2 55.5 -> 32.1 us, 2048^2 229 -> 147
+// us; 128^2 12.6 -> 4.7 us.
+template <int TX, int TY, class Codec, class L, class LH, bool kGen, bool kWalls>
 __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     k_dev_fused2d(Geo g, Coef<float> Kin, DevStep b, int tiles_x, int ntiles) {
   const Coef<float> K = variant<kGen>(Kin);
@@ -863,6 +863,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
   using Shape = TileShape<TX, TY>;
   constexpr int BX = Shape::BX, BY = Shape::BY, NT = Shape::NT;
   constexpr int AX = BX + 2, AY = BY + 2;
+  constexpr int TILE_PER_THREAD = (AX * AY + NT - 1) / NT;
   __shared__ float phiA[AY][AX];  // phi^n on T+2
   __shared__ float lamA[AY][AX];  // Lambda^{n-1} on T+2
   __shared__ float phiB[BY][BX];  // phi^{n+1} on T+1
@@ -873,178 +874,174 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
   Shape::node(threadIdx.x, tx, ty, valid);
 
   for (int tile = first_tile(); tile < ntiles; tile += gridDim.x) {
-  const int X0 = (tile % tiles_x) * TX, Y0 = (tile / tiles_x) * TY;
-  for (int l = threadIdx.x; l < AX * AY; l += NT) {
-    const int lx = l % AX, ly = l / AX;
-    int vx = X0 - 2 + lx, vy = Y0 - 2 + ly;
-    vx = g.bcx ? min(max(vx, 0), g.nx - 1) : wrap_coord(vx, g.nx);
-    vy = g.bcy ? min(max(vy, 0), g.ny - 1) : wrap_coord(vy, g.ny);
-    const int64_t j = node_index(g, vx, vy, 0);
-    phiA[ly][lx] = b.cur.PHI[j];
-    lamA[ly][lx] = b.cur.LAM[j];
-  }
+    const int X0 = (tile % tiles_x) * TX, Y0 = (tile / tiles_x) * TY;
+    const int ux = X0 - 1 + tx, uy = Y0 - 1 + ty;  // unwrapped node of this thread
+    const bool active = valid && (!kWalls || ((!g.bcx || (ux >= 0 && ux < g.nx)) &&
+                                              (!g.bcy || (uy >= 0 && uy < g.ny))));
+    const bool out = valid && ux < g.nx && uy < g.ny && tx >= 1 && tx <= TX && ty >= 1 && ty <= TY;
+    const Pull2D<kWalls> at(g, ux, uy);
+    const int64_t i = at.self();
+    auto mh = [](int k) { return mslot<LH>(k); };
+    auto mg = [](int k) { return mslot<L>(k); };
 
-  const int ux = X0 - 1 + tx, uy = Y0 - 1 + ty;  // unwrapped node of this thread
-  const bool in_x = ux >= 0 && ux < g.nx, in_y = uy >= 0 && uy < g.ny;
-  const bool active = valid && (in_x || !g.bcx) && (in_y || !g.bcy);
-  const bool out = valid && in_x && in_y && tx >= 1 && tx <= TX && ty >= 1 && ty <= TY;
-  const int x = g.bcx ? ux : wrap_coord(ux, g.nx);
-  const int y = g.bcy ? uy : wrap_coord(uy, g.ny);
-  const int64_t i = active ? node_index(g, x, y, 0) : 0;
-  const int xm = (g.bcx && ux == 0) ? 0 : -1, xp = (g.bcx && ux == g.nx - 1) ? 0 : 1;
-  const int ym = (g.bcy && uy == 0) ? 0 : -1, yp = (g.bcy && uy == g.ny - 1) ? 0 : 1;
-  // population k (of lattice P) of this node comes from x - e_k, or bounces
-  // back at a wall
-  auto inside = [&](auto tag, int k) {
-    using P = typename decltype(tag)::type;
-    const int sx = ux - P::ex[k], sy = uy - P::ey[k];
-    return !((g.bcx && (sx < 0 || sx >= g.nx)) || (g.bcy && (sy < 0 || sy >= g.ny)));
-  };
-  // pull of population k from a distribution in the deviation format, the
-  // reference field of the source node read from its T+2 tile
-  auto pull_tile = [&](auto tag, const DevDist& d, const float (*ref)[AX], int k) -> float {
-    using P = typename decltype(tag)::type;
-    if (k == P::REST) return d.rest[i];
-    int sx = x, sy = y, kk = k, rx = tx + 1, ry = ty + 1;
-    if (inside(tag, k)) {
-      pull_axis(sx, P::ex[k], g.nx, g.bcx);
-      pull_axis(sy, P::ey[k], g.ny, g.bcy);
-      rx -= P::ex[k];
-      ry -= P::ey[k];
-    } else {
-      kk = P::opp[k];
-    }
-    const float r = float(P::w[kk]) * ref[ry][rx];
-    return dev_decode<Codec>(d.mov[mov_index<P>(g, kk, sx, sy, 0)], r);
-  };
-  const LatticeTag<L> tg{};
-  const LatticeTag<LH> th{};
-  __syncthreads();
-
-  float gn[Q];          // g~^{n+1}
-  float hdec[QH];       // h~*^n as readers decode it
-  float phin = 0.0f;
-  if (active) {
-    float h[QH];
-    double c = 0.0;
+    // every load of the tile in one batch before the first barrier: the codes
+    // (of inactive nodes too, in range and not used) and the reference tiles
+    float pv[TILE_PER_THREAD], lv[TILE_PER_THREAD];
+    uint16_t ch[QH], cg[Q];
 #pragma unroll
-    for (int k = 0; k < QH; ++k) {
-      h[k] = pull_tile(th, b.cur.H, lamA, k);
-      c = k == 0 ? double(h[k]) : c + double(h[k]);
+    for (int j = 0; j < TILE_PER_THREAD; ++j) {
+      const int l = min((int)threadIdx.x + j * NT, AX * AY - 1);
+      int vx = X0 - 2 + l % AX, vy = Y0 - 2 + l / AX;
+      vx = kWalls && g.bcx ? min(max(vx, 0), g.nx - 1) : wrap_near(vx, g.nx);
+      vy = kWalls && g.bcy ? min(max(vy, 0), g.ny - 1) : wrap_near(vy, g.ny);
+      const int64_t q = (int64_t)vy * g.nx + vx;
+      pv[j] = b.cur.PHI[q];
+      lv[j] = b.cur.LAM[q];
     }
-    double sg = 0.0;
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-      gn[k] = pull_tile(tg, b.cur.G, phiA, k);
-      sg = k == 0 ? double(gn[k]) : sg + double(gn[k]);
-    }
-    const float phi = phiA[ty + 1][tx + 1];
-    const float mu = float(closure(K.q, c, double(phi)));
-    auto at = [&](int dx, int dy, int) -> float {
-      const int ox = dx < 0 ? xm : (dx > 0 ? xp : 0);
-      const int oy = dy < 0 ? ym : (dy > 0 ? yp : 0);
-      return phiA[ty + 1 + oy][tx + 1 + ox];
-    };
-    float gr[3], n[3];
-    gradient_normal<L, float>(at, K.eps2, gr, n);
-    const float sbar = source_moment<float>(K, phi, mu);
-    phin = float(sg + 0.5 * double(sbar));
-    float F[3];
-    h_flux<L, float>(K, mu, gr, n, phin - phi, K.anti_trapping != 0, F);
-    const float lam = h_lambda<float>(K, phi, mu);
-    const float cc = float(c);
-    float hs[QH];
 #pragma unroll
     for (int k = 0; k < QH; ++k)
-      hs[k] = h_update<LH, float>(K, k, h[k], cc, lam, F);
-    uint16_t enc[QH];
-    encode_h<Codec, LH>(hs, lam, c, enc, hdec);
-    if (out) {
+      ch[k] = k == LH::REST ? uint16_t(0) : b.cur.H.mov[at.template slot<LH>(k, mh)];
 #pragma unroll
-      for (int k = 0; k < QH; ++k)
-        if (k != LH::REST) b.nxt.H.mov[mov_index<LH>(g, k, x, y, 0)] = enc[k];
-      b.nxt.H.rest[i] = hdec[LH::REST];
-      b.nxt.LAM[i] = lam;
-      b.nxt.PHI[i] = phin;
-    }
-  }
-  if (valid) {
-    phiB[ty][tx] = phin;
-    if (active) {
+    for (int k = 0; k < Q; ++k)
+      cg[k] = k == L::REST ? uint16_t(0) : b.cur.G.mov[at.template slot<L>(k, mg)];
+    const float h_rest = b.cur.H.rest[i], g_rest = b.cur.G.rest[i];
 #pragma unroll
-      for (int k = 0; k < QH; ++k)
-        if (k != LH::REST) hx[k][ty][tx] = hdec[k];
+    for (int j = 0; j < TILE_PER_THREAD; ++j) {
+      const int l = threadIdx.x + j * NT;
+      if (l < AX * AY) {
+        phiA[l / AX][l % AX] = pv[j];
+        lamA[l / AX][l % AX] = lv[j];
+      }
     }
-  }
-  __syncthreads();
+    __syncthreads();
 
-  if (out) {
-    double c1 = 0.0;
+    // decoded with the reference of the source node, or of the node itself
+    // for a bounced population (w_opp(k) = w_k)
+    const float lam0 = lamA[ty + 1][tx + 1], phi = phiA[ty + 1][tx + 1];
+    float gn[Q];     // g~^{n+1}
+    float hdec[QH];  // h~*^n as readers decode it
+    double sg = 0.0;
+    {
+      float h[QH];
+      double c = 0.0;
 #pragma unroll
-    for (int k = 0; k < QH; ++k) {
-      float v;
-      if (k == LH::REST)
-        v = hdec[k];
-      else if (inside(th, k))
-        v = hx[k][ty - LH::ey[k]][tx - LH::ex[k]];
-      else
-        v = hdec[LH::opp[k]];
-      c1 = k == 0 ? double(v) : c1 + double(v);
-    }
-    const float phi1 = phiB[ty][tx];
-    const float mu1 = float(closure(K.q, c1, double(phi1)));
-    auto at1 = [&](int dx, int dy, int) -> float {
-      const int ox = dx < 0 ? xm : (dx > 0 ? xp : 0);
-      const int oy = dy < 0 ? ym : (dy > 0 ? yp : 0);
-      return phiB[ty + oy][tx + ox];
-    };
-    float gr[3], n[3];
-    gradient_normal<L, float>(at1, K.eps2, gr, n);
-    float G[Q], gs[Q];
-    phi_sources<L, float>(K, phi1, mu1, n, G);
-    double sg1 = 0.0;
+      for (int k = 0; k < QH; ++k) {
+        if (k == LH::REST) {
+          h[k] = h_rest;
+        } else {
+          const float in = lamA[ty + 1 - LH::ey[k]][tx + 1 - LH::ex[k]];
+          h[k] = dev_decode<Codec>(ch[k], float(LH::w[k]) * (at.template bounced<LH>(k) ? lam0 : in));
+        }
+        c = k == 0 ? double(h[k]) : c + double(h[k]);
+      }
 #pragma unroll
-    for (int k = 0; k < Q; ++k) {
-      sg1 = k == 0 ? double(gn[k]) : sg1 + double(gn[k]);
-      gs[k] = g_collide<L, float>(K, k, gn[k], phi1, G[k]);
-    }
-    uint16_t genc[Q];
-    float gdec[Q];
-    encode_g<Codec, L>(gs, phi1, genc, gdec);
-    balance_g_rest<L, float, float>(K, gdec, sg1, phi1, source_moment<float>(K, phi1, mu1));
+      for (int k = 0; k < Q; ++k) {
+        if (k == L::REST) {
+          gn[k] = g_rest;
+        } else {
+          const float in = phiA[ty + 1 - L::ey[k]][tx + 1 - L::ex[k]];
+          gn[k] = dev_decode<Codec>(cg[k], float(L::w[k]) * (at.template bounced<L>(k) ? phi : in));
+        }
+        sg = k == 0 ? double(gn[k]) : sg + double(gn[k]);
+      }
+      const float mu = float(closure(K.q, c, double(phi)));
+      auto atA = [&](int dx, int dy, int) -> float {
+        return phiA[ty + 1 + at.sy(dy)][tx + 1 + at.sx(dx)];
+      };
+      float gr[3], n[3];
+      gradient_normal<L, float>(atA, K.eps2, gr, n);
+      const float sbar = source_moment<float>(K, phi, mu);
+      const float phin = float(sg + 0.5 * double(sbar));
+      float F[3];
+      h_flux<L, float>(K, mu, gr, n, phin - phi, K.anti_trapping != 0, F);
+      const float lam = h_lambda<float>(K, phi, mu);
+      const float cc = float(c);
+      float hs[QH];
 #pragma unroll
-    for (int k = 0; k < Q; ++k) {
-      if (k == L::REST)
-        b.nxt.G.rest[i] = gdec[k];
-      else
-        b.nxt.G.mov[mov_index<L>(g, k, x, y, 0)] = genc[k];
+      for (int k = 0; k < QH; ++k) hs[k] = h_update<LH, float>(K, k, h[k], cc, lam, F);
+      uint16_t enc[QH];
+      encode_h<Codec, LH>(hs, lam, c, enc, hdec);
+      if (active) {
+        phiB[ty][tx] = phin;
+#pragma unroll
+        for (int k = 0; k < QH; ++k)
+          if (k != LH::REST) hx[k][ty][tx] = hdec[k];
+      }
+      if (out) {
+#pragma unroll
+        for (int k = 0; k < QH; ++k)
+          if (k != LH::REST) b.nxt.H.mov[mh(k) * at.plane + i] = enc[k];
+        b.nxt.H.rest[i] = hdec[LH::REST];
+        b.nxt.LAM[i] = lam;
+        b.nxt.PHI[i] = phin;
+      }
     }
-  }
-  __syncthreads();  // the LDS tiles are refilled by the next tile
+    __syncthreads();
+
+    if (out) {
+      double c1 = 0.0;
+#pragma unroll
+      for (int k = 0; k < QH; ++k) {
+        float v = hdec[k];
+        if (k != LH::REST) {
+          const float in = hx[k][ty - LH::ey[k]][tx - LH::ex[k]];
+          v = at.template bounced<LH>(k) ? hdec[LH::opp[k]] : in;
+        }
+        c1 = k == 0 ? double(v) : c1 + double(v);
+      }
+      const float phi1 = phiB[ty][tx];
+      const float mu1 = float(closure(K.q, c1, double(phi1)));
+      auto atB = [&](int dx, int dy, int) -> float {
+        return phiB[ty + at.sy(dy)][tx + at.sx(dx)];
+      };
+      float gr[3], n[3];
+      gradient_normal<L, float>(atB, K.eps2, gr, n);
+      float G[Q], gs[Q];
+      phi_sources<L, float>(K, phi1, mu1, n, G);
+#pragma unroll
+      for (int k = 0; k < Q; ++k) gs[k] = g_collide<L, float>(K, k, gn[k], phi1, G[k]);
+      uint16_t genc[Q];
+      float gdec[Q];
+      encode_g<Codec, L>(gs, phi1, genc, gdec);
+      balance_g_rest<L, float, float>(K, gdec, sg, phi1, source_moment<float>(K, phi1, mu1));
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        if (k == L::REST)
+          b.nxt.G.rest[i] = gdec[k];
+        else
+          b.nxt.G.mov[mg(k) * at.plane + i] = genc[k];
+      }
+    }
+    __syncthreads();  // the LDS tiles are refilled by the next tile
   }
 }
 
-// output rows per tile of the fused 2-D deviation kernel: 64 x 13 outputs,
-// 1024 threads, one block per CU (1024^2 step: 55 us, against 62 / 70 / 74 /
-// 78 us at 12 / 8 / 5 / 4 rows, the last two with two blocks per CU)
-#ifndef GPLBM_DEV2_TY
-#define GPLBM_DEV2_TY 13
-#endif
-
 template <class Codec, class L, class LH, bool kGen>
 struct DevFused2D {
-  static int launch(const Geo& g, const Coef<float>& K, const DevStep& b, hipStream_t st) {
-    constexpr int TX = 64, TY = GPLBM_DEV2_TY;
+  template <int TY, bool kWalls>
+  static int run(const Geo& g, const Coef<float>& K, const DevStep& b, hipStream_t st) {
+    constexpr int TX = 64;
     constexpr int NT = TileShape<TX, TY>::NT;
-    auto kernel = k_dev_fused2d<TX, TY, Codec, L, LH, kGen>;
+    auto kernel = k_dev_fused2d<TX, TY, Codec, L, LH, kGen, kWalls>;
     const int tiles_x = (g.nx + TX - 1) / TX;
     const int tiles_y = (g.ny + TY - 1) / TY;
     const int ntiles = tiles_x * tiles_y;
     static int resident[64] = {0};
     const int slots = resident_slots(kernel, NT, resident);
     if (slots <= 0) return -1;
-    hipLaunchKernelGGL(kernel, dim3(resident_grid(slots, ntiles)), dim3(NT), 0, st, g, K, b, tiles_x, ntiles);
+    hipLaunchKernelGGL(kernel, dim3(resident_grid(slots, ntiles)), dim3(NT), 0, st, g, K, b, tiles_x,
+                       ntiles);
     return 0;
+  }
+  template <bool kWalls>
+  static int by_rows(const Geo& g, const Coef<float>& K, const DevStep& b, hipStream_t st) {
+    const int rows = tile_rows(g.nx, g.ny, 64, false);
+    if (rows == 1) return run<1, kWalls>(g, K, b, st);
+    if (rows == 4) return run<4, kWalls>(g, K, b, st);
+    return run<8, kWalls>(g, K, b, st);
+  }
+  static int launch(const Geo& g, const Coef<float>& K, const DevStep& b, hipStream_t st) {
+    return (g.bcx || g.bcy) ? by_rows<true>(g, K, b, st) : by_rows<false>(g, K, b, st);
   }
 };
 

@@ -27,6 +27,15 @@ __device__ __forceinline__ int wrap_coord(int u, int n) {
   return v < 0 ? v + n : v;
 }
 
+// The same for the coordinates of a tile's nodes without a division: u in
+// [-2, n + 1] wraps; a u further off (a node of a ragged tile that no output
+// reads) only stays in range.
+__device__ __forceinline__ int wrap_near(int u, int n) {
+  u = u < 0 ? u + n : u;
+  u = u >= n ? u - n : u;
+  return min(max(u, 0), n - 1);
+}
+
 template <int TX_, int TY_>
 struct TileShape {
   static constexpr int TX = TX_, TY = TY_;
