@@ -28,13 +28,22 @@ namespace gplbm {
 
 struct F16Codec {
   static constexpr float kScale = 4096.0f, kInv = 1.0f / 4096.0f;
-  __device__ static uint16_t enc(float v) { return __builtin_bit_cast(uint16_t, (_Float16)v); }
-  __device__ static float dec(uint16_t u) { return (float)__builtin_bit_cast(_Float16, u); }
+  __device__ static uint16_t enc(float v, float ref) {
+    return __builtin_bit_cast(uint16_t, (_Float16)((v - ref) * kScale));
+  }
+  // r (ref + delta / S), r a power of two: one mixed-precision multiply-add
+  __device__ static float dec(uint16_t u, float ref, float r) {
+    return __builtin_fmaf((float)__builtin_bit_cast(_Float16, u), kInv * r, ref);
+  }
 };
 struct BF16Codec {
   static constexpr float kScale = 1.0f, kInv = 1.0f;
-  __device__ static uint16_t enc(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
-  __device__ static float dec(uint16_t u) { return (float)__builtin_bit_cast(__bf16, u); }
+  __device__ static uint16_t enc(float v, float ref) {
+    return __builtin_bit_cast(uint16_t, (__bf16)(v - ref));
+  }
+  __device__ static float dec(uint16_t u, float ref, float r) {
+    return __builtin_fmaf((float)__builtin_bit_cast(__bf16, u), r, ref);
+  }
 };
 
 // one distribution in the deviation format
@@ -80,11 +89,47 @@ __device__ __forceinline__ int64_t mov_index(const Geo& g, int k, int x, int y, 
 
 template <class Codec>
 __device__ __forceinline__ float dev_decode(uint16_t raw, float ref) {
-  return ref + Codec::dec(raw) * Codec::kInv;
+  return Codec::dec(raw, ref, 1.0f);
 }
 template <class Codec>
 __device__ __forceinline__ uint16_t dev_encode(float v, float ref) {
-  return Codec::enc((v - ref) * Codec::kScale);
+  return Codec::enc(v, ref);
+}
+
+// The moving weights of every lattice are powers of two apart, so a tile may
+// hold the reference field times the smallest of them, w_min: the value of
+// population k is then w_k / w_min times a sum with that one operand, exactly
+// the sum with w_k ref.
+template <class L>
+constexpr double min_weight() {
+  double w = 1.0;
+  for (int k = 0; k < L::Q; ++k)
+    if (k != L::REST && L::w[k] < w) w = L::w[k];
+  return w;
+}
+template <class L>
+constexpr int weight_ratio(int k) {
+  return int(L::w[k] / min_weight<L>() + 0.5);
+}
+template <class L>
+constexpr bool weights_scale() {
+  for (int k = 0; k < L::Q; ++k) {
+    const int r = weight_ratio<L>(k);
+    if (k != L::REST && ((r & (r - 1)) || float(L::w[k]) != r * float(min_weight<L>())))
+      return false;
+  }
+  return true;
+}
+static_assert(weights_scale<D3Q19>() && weights_scale<D3Q7>() && weights_scale<D2Q9>() &&
+              weights_scale<D2Q5>(), "moving weights are w_min times powers of two");
+
+// Value of population k from its code and wref = w_min times the reference
+// field of the node that wrote it.
+template <class Codec, class L>
+__device__ __forceinline__ float dev_decode_wmin(int k, uint16_t raw, float wref) {
+  const int r = weight_ratio<L>(k);
+  const float v = Codec::dec(raw, wref, 1.0f / r);
+  return r == 1 ? v : r * v;
 }
 
 // Pull of population k at (x, y, z) from a distribution in the deviation
@@ -260,9 +305,7 @@ __global__ void __launch_bounds__(256) k_dev_split_h(Geo g, Coef<float> K, DevSt
   const float lam = h_lambda<float>(K, phi, mu);
   const float cc = float(c);
   float hs[LH::Q];
-#pragma unroll
-  for (int k = 0; k < LH::Q; ++k)
-    hs[k] = h_update<LH, float>(K, k, h[k], cc, lam, F);
+  h_update<LH>(K, h, cc, lam, F, hs);
   uint16_t enc[LH::Q];
   float hdec[LH::Q];
   encode_h<Codec, LH>(hs, lam, c, enc, hdec);
@@ -407,18 +450,20 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
   constexpr int BX = Shape::BX, BY = Shape::BY;
   constexpr int AX = BX + 2, AY = BY + 2;
   constexpr int NT = Shape::NT;
+  constexpr int TILE_PER_THREAD = (AX * AY + NT - 1) / NT;
   // Rings of four planes and a double-buffered exchange, so that one barrier
   // per plane orders every LDS access: the tile of plane p + 2 is loaded, and
   // the next plane's exchange written, while other waves still read the
   // planes of p (see the hazards noted at the barrier).
   __shared__ float phiA[4][AY][AX];          // phi^n, planes p-1 .. p+2
-  __shared__ float lamA[4][AY][AX];          // Lambda^{n-1}, planes p-1 .. p+2
+  __shared__ float lamA[4][AY][AX];          // w_min Lambda^{n-1}, planes p-1 .. p+2
   __shared__ float phiB[4][BY][BX];          // phi^{n+1}, planes p-3 .. p
   constexpr int QH = LH::Q;  // h lattice (D3Q19 or D3Q7)
+  constexpr float kWmin = float(min_weight<LH>());
   // e_z layers of the h lattice: +1 at [0, NU), 0 at [NU, NU + NM), -1 after
   constexpr int NU = count_ez<LH>(1), NM = count_ez<LH>(0);
-  // Exchange of plane p: the 16-bit codes of the moving h*^n and Lambda^n,
-  // their reference.  Periodic: every moving population in hxe and Lambda in
+  // Exchange of plane p: the 16-bit codes of the moving h*^n and w_min
+  // Lambda^n, their reference.  Periodic: every moving population in hxe and Lambda in
   // hxl, by plane parity.  Walls: the e_z = +1 layer in hxu and Lambda in hxl
   // by plane modulo 3 (the plane above gathers that layer after its own
   // barrier, and a node's own entries there are the bounce of its e_z = -1
@@ -450,8 +495,8 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
   bool active = valid;
   if constexpr (kWalls)
     active = valid && (!g.bcx || (ux >= 0 && ux < nx)) && (!g.bcy || (uy >= 0 && uy < ny));
-  const int x = kWalls ? tile_coord(ux, nx, g.bcx) : wrap_coord(ux, nx);
-  const int y = kWalls ? tile_coord(uy, ny, g.bcy) : wrap_coord(uy, ny);
+  const int x = kWalls ? tile_coord(ux, nx, g.bcx) : wrap_near(ux, nx);
+  const int y = kWalls ? tile_coord(uy, ny, g.bcy) : wrap_near(uy, ny);
   // source offsets wrap also on wall axes: a source beyond a wall is never
   // read (its population bounces), the wrapped address only keeps it in range
   const int xo[3] = {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1};
@@ -476,14 +521,30 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     yp = (g.bcy && uy == ny - 1) ? 0 : 1;
   }
 
+  // tile positions this thread loads (T+2 in x-y; clamped along wall axes, the
+  // mirror ghost): byte offset in a plane of PHI / LAM and slot in a ring plane
+  uint32_t tile_off[TILE_PER_THREAD];
+#pragma unroll
+  for (int j = 0; j < TILE_PER_THREAD; ++j) {
+    const int l = min((int)threadIdx.x + j * NT, AX * AY - 1);
+    const int vx = X0 - 2 + l % AX, vy = Y0 - 2 + l / AX;
+    const int gx = kWalls ? tile_coord(vx, nx, g.bcx) : wrap_near(vx, nx);
+    const int gy = kWalls ? tile_coord(vy, ny, g.bcy) : wrap_near(vy, ny);
+    tile_off[j] = uint32_t(gy * nx + gx) * 4u;
+  }
   auto load_tiles = [&](int p) {
     const int64_t zoff = (int64_t)(kWalls ? tile_coord(p, nz, g.bcz) : wrap_coord(p, nz)) * plane;
-    for (int l = threadIdx.x; l < AX * AY; l += NT) {
-      const int lx = l % AX, ly = l / AX;
-      const int gx = kWalls ? tile_coord(X0 - 2 + lx, nx, g.bcx) : wrap_coord(X0 - 2 + lx, nx);
-      const int gy = kWalls ? tile_coord(Y0 - 2 + ly, ny, g.bcy) : wrap_coord(Y0 - 2 + ly, ny);
-      phiA[ring4(p)][ly][lx] = b.cur.PHI[zoff + gy * nx + gx];
-      lamA[ring4(p)][ly][lx] = b.cur.LAM[zoff + gy * nx + gx];
+    const auto P = make_rsrc(b.cur.PHI + zoff, uint32_t(plane) * 4u);
+    const auto Lm = make_rsrc(b.cur.LAM + zoff, uint32_t(plane) * 4u);
+    float* const pa = &phiA[ring4(p)][0][0];
+    float* const la = &lamA[ring4(p)][0][0];
+#pragma unroll
+    for (int j = 0; j < TILE_PER_THREAD; ++j) {
+      const int l = threadIdx.x + j * NT;
+      if ((j + 1) * NT <= AX * AY || l < AX * AY) {
+        pa[l] = bload<float>(P, tile_off[j], 0);
+        la[l] = kWmin * bload<float>(Lm, tile_off[j], 0);
+      }
     }
   };
   // first plane: the halo plane below the chunk, or the bottom plane at a z wall
@@ -500,7 +561,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
   // e_z = +1 populations arrive one plane early, the e_z = -1 ones one plane
   // late, each group gathered in ascending k
   const bool inner = valid && tx >= 1 && tx <= TX && ty >= 1 && ty <= TY;
-  double acc_dn = 0.0, acc_mid = 0.0;
+  double acc_dn = 0.0, acc_mid = 0.0, sg_old = 0.0;
 
   for (int p = pfirst; p <= z1; ++p) {
     // past a top wall: no plane, only the completion of plane nz - 1
@@ -529,6 +590,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     const int sA = ring4(p);
 
     float g_new[Q];
+    double sg = 0.0;
     float hdec[QH];
     float phin = 0.0f, lam = 0.0f;
     uint16_t enc[QH];
@@ -536,7 +598,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
       // pulls, decoded with the reference of the source node (LDS tiles), or
       // of the node itself for a population bounced back at a wall
       float h[QH];
-      double c = 0.0, sg = 0.0;
+      double c = 0.0;
       // populations bounced at a wall (bits k); a wavefront with none (all but
       // those of the tiles at a wall) takes the plain pulls
       uint32_t bh = 0u, bg = 0u;
@@ -581,7 +643,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
             v = b.cur.H.rest[selfnode];
           } else {
             const float src = lamA[ring4(p - LH::ez[k])][ty + 1 - LH::ey[k]][tx + 1 - LH::ex[k]];
-            v = dev_decode<Codec>(ch[k], float(LH::w[k]) * (((bh >> k) & 1u) ? lam_own : src));
+            v = dev_decode_wmin<Codec, LH>(k, ch[k], ((bh >> k) & 1u) ? lam_own : src);
           }
           h[k] = v;
           c = k == 0 ? double(v) : c + double(v);
@@ -599,31 +661,37 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
           sg = k == 0 ? double(v) : sg + double(v);
         }
       } else {
+        // every pull in one batch before the first decode: left to itself the
+        // scheduler may interleave loads and decodes, and the wave then waits
+        // for memory once per population
+        uint16_t ch[QH], cg[Q];
+        const float h_rest = b.cur.H.rest[selfnode], g_rest = b.cur.G.rest[selfnode];
+#pragma unroll
+        for (int k = 0; k < QH; ++k)
+          ch[k] = k == LH::REST ? uint16_t(0)
+                                : bload16(Hz[1 - LH::ez[k]], xyb[1 - LH::ey[k]][1 - LH::ex[k]],
+                                          mslot<LH>(k) * planeB);
+#pragma unroll
+        for (int k = 0; k < Q; ++k)
+          cg[k] = k == LG::REST ? uint16_t(0)
+                                : bload16(Gz[1 - LG::ez[k]], xyb[1 - LG::ey[k]][1 - LG::ex[k]],
+                                          mslot<LG>(k) * planeB);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < QH; ++k) {
-          float v;
-          if (k == LH::REST) {
-            v = b.cur.H.rest[selfnode];
-          } else {
-            const float ref = float(LH::w[k]) *
-                              lamA[ring4(p - LH::ez[k])][ty + 1 - LH::ey[k]][tx + 1 - LH::ex[k]];
-            v = dev_decode<Codec>(bload16(Hz[1 - LH::ez[k]], xyb[1 - LH::ey[k]][1 - LH::ex[k]],
-                                          mslot<LH>(k) * planeB), ref);
-          }
+          float v = h_rest;
+          if (k != LH::REST)
+            v = dev_decode_wmin<Codec, LH>(
+                k, ch[k], lamA[ring4(p - LH::ez[k])][ty + 1 - LH::ey[k]][tx + 1 - LH::ex[k]]);
           h[k] = v;
           c = k == 0 ? double(v) : c + double(v);
         }
 #pragma unroll
         for (int k = 0; k < Q; ++k) {
-          float v;
-          if (k == LG::REST) {
-            v = b.cur.G.rest[selfnode];
-          } else {
-            const float ref = float(LG::w[k]) *
-                              phiA[ring4(p - LG::ez[k])][ty + 1 - LG::ey[k]][tx + 1 - LG::ex[k]];
-            v = dev_decode<Codec>(bload16(Gz[1 - LG::ez[k]], xyb[1 - LG::ey[k]][1 - LG::ex[k]],
-                                          mslot<LG>(k) * planeB), ref);
-          }
+          float v = g_rest;
+          if (k != LG::REST)
+            v = dev_decode<Codec>(cg[k], float(LG::w[k]) * phiA[ring4(p - LG::ez[k])]
+                                                               [ty + 1 - LG::ey[k]][tx + 1 - LG::ex[k]]);
           g_new[k] = v;
           sg = k == 0 ? double(v) : sg + double(v);
         }
@@ -642,9 +710,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
       lam = h_lambda<float>(K, phi, mu);
       const float cc = float(c);
       float hs[QH];
-#pragma unroll
-      for (int k = 0; k < QH; ++k)
-        hs[k] = h_update<LH, float>(K, k, h[k], cc, lam, F);
+      h_update<LH>(K, h, cc, lam, F, hs);
       encode_h<Codec, LH>(hs, lam, c, enc, hdec);
     }
     if (active && !closing) phiB[sA][ty][tx] = phin;
@@ -677,7 +743,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
         else
           hxe[xb][kWalls ? k - NU - 1 : mslot<LH>(k)][ty][tx] = enc[k];
       }
-      hxl[lb][ty][tx] = lam;
+      hxl[lb][ty][tx] = kWmin * lam;
     }
     load_tiles(p + 2);
     // The one barrier of the plane.  Before it: reads of the phi / Lambda
@@ -694,14 +760,14 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     // exchange of plane p (not the e_z = +1 layer with walls)
     auto xchg = [&](int k) -> double {
       const int sy = ty - LH::ey[k], sx = tx - LH::ex[k];
-      const float ref = float(LH::w[k]) * hxl[lb][sy][sx];
-      return double(dev_decode<Codec>(hxe[xb][kWalls ? k - NU - 1 : mslot<LH>(k)][sy][sx], ref));
+      return double(dev_decode_wmin<Codec, LH>(
+          k, hxe[xb][kWalls ? k - NU - 1 : mslot<LH>(k)][sy][sx], hxl[lb][sy][sx]));
     };
     // walls: decoded e_z = +1 population k of plane p - 1 at region node
     // (sy, sx)
     auto xup = [&](int k, int sy, int sx) -> double {
-      const float ref = float(LH::w[k]) * hxl[kWalls ? pb : 0][sy][sx];
-      return double(dev_decode<Codec>(hxu[kWalls ? pb : 0][kWalls ? k : 0][sy][sx], ref));
+      return double(dev_decode_wmin<Codec, LH>(k, hxu[kWalls ? pb : 0][kWalls ? k : 0][sy][sx],
+                                               hxl[kWalls ? pb : 0][sy][sx]));
     };
     double acc_up = 0.0;
     if constexpr (!kWalls) {
@@ -770,16 +836,13 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
       gradient_normal<LG, float>(atB, K.eps2, gr1, n1);
       float G[Q], gs[Q];
       phi_sources<LG, float>(K, phi1, mu1, n1, G);
-      double sg1 = 0.0;
 #pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        sg1 = k == 0 ? double(g_old[k]) : sg1 + double(g_old[k]);
-        gs[k] = g_collide<LG, float>(K, k, g_old[k], phi1, G[k]);
-      }
+      for (int k = 0; k < Q; ++k) gs[k] = g_collide<LG, float>(K, k, g_old[k], phi1, G[k]);
       uint16_t genc[Q];
       float gdec[Q];
       encode_g<Codec, LG>(gs, phi1, genc, gdec);
-      balance_g_rest<LG, float, float>(K, gdec, sg1, phi1, source_moment<float>(K, phi1, mu1));
+      // sg_old: the double sum of these g, taken when they were pulled
+      balance_g_rest<LG, float, float>(K, gdec, sg_old, phi1, source_moment<float>(K, phi1, mu1));
       const auto Gw = make_rsrc(reinterpret_cast<char*>(b.nxt.G.mov) + zq * groupB, uint32_t(groupB));
 #pragma unroll
       for (int k = 0; k < Q; ++k)
@@ -788,6 +851,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     }
 #pragma unroll
     for (int k = 0; k < Q; ++k) g_old[k] = g_new[k];
+    sg_old = sg;
     if constexpr (kWalls) {
       acc_dn = acc_up;
     } else {
@@ -957,8 +1021,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
       const float lam = h_lambda<float>(K, phi, mu);
       const float cc = float(c);
       float hs[QH];
-#pragma unroll
-      for (int k = 0; k < QH; ++k) hs[k] = h_update<LH, float>(K, k, h[k], cc, lam, F);
+      h_update<LH>(K, h, cc, lam, F, hs);
       uint16_t enc[QH];
       encode_h<Codec, LH>(hs, lam, c, enc, hdec);
       if (active) {

@@ -168,8 +168,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT), (sizeof(S) == 4 ? 6 :
       h_flux<L, C>(K, mu, gr, n, phin - phi, K.anti_trapping != 0, F);
       const C lam = h_lambda<C>(K, phi, mu);
       const C cc = C(c);
-#pragma unroll
-      for (int k = 0; k < LH::Q; ++k) hs[k] = C(S(h_update<LH, C>(K, k, h[k], cc, lam, F)));
+      h_update<LH>(K, h, cc, lam, F, hs);
       balance_rest<LH, S, C>(hs, c);
       if (active) {
         phiB[ty][tx] = phin;

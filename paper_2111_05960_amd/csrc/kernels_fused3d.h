@@ -397,8 +397,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
         h_flux<L, C>(K, mu, gr, n, dtphi, K.anti_trapping != 0, F);
         const C lam = h_lambda<C>(K, phi, mu);
         const C cc = C(c);
-#pragma unroll
-        for (int k = 0; k < QH; ++k) hs[k] = C(S(h_update<LH, C>(K, k, h[k], cc, lam, F)));
+        h_update<LH>(K, h, cc, lam, F, hs);
         balance_rest<LH, S, C>(hs, c);
 
         if (out && own_p) {

@@ -83,8 +83,7 @@ __global__ void __launch_bounds__(256) k_split_h(Geo g, Coef<C> Kin, StepBufs<S>
   const C lam = h_lambda<C>(K, phi, mu);
   const C cc = C(c);
   C hs[LH::Q];
-#pragma unroll
-  for (int k = 0; k < LH::Q; ++k) hs[k] = C(S(h_update<LH, C>(K, k, h[k], cc, lam, F)));
+  h_update<LH>(K, h, cc, lam, F, hs);
   balance_rest<LH, S, C>(hs, c);
 #pragma unroll
   for (int k = 0; k < LH::Q; ++k) b.Hn[pop_index<LH>(g, k, x, y, z)] = S(hs[k]);
