@@ -111,7 +111,10 @@ extern "C" {
 #define GPLBM_BF16_DEV 3
 
 /* kernel schedule */
-#define GPLBM_SCHED_AUTO 0  /* fused when the geometry allows it, else split */
+#define GPLBM_SCHED_AUTO 0  /* fused when the geometry allows it, else split; where the
+                               two kernels of the split schedule are the faster (small
+                               3-D grids, deviation formats with walls) a fused AUTO
+                               context steps with them: the same bits */
 #define GPLBM_SCHED_SPLIT 1 /* two kernels per step */
 #define GPLBM_SCHED_FUSED 2 /* one kernel per step (tile halo recompute) */
 

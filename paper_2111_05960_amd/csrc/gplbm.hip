@@ -44,6 +44,7 @@ struct gplbm_ctx {
   int64_t step;
   bool ready;
   int sched;
+  bool node_steps;    // a fused context whose steps run as the per-node pair
   hipStream_t stream;
   int device;
   std::string err;
@@ -229,6 +230,35 @@ Geo make_geo(const gplbm_params& p) {
   return g;
 }
 
+// The context's steps run the fused kernel of its lattice.
+bool fused_steps(const gplbm_ctx* ctx) {
+  return ctx->sched == GPLBM_SCHED_FUSED && !ctx->node_steps;
+}
+
+template <class T>
+struct Tag {
+  using type = T;
+};
+
+// Launch of a per-node kernel in the addressing that serves the grid: f(tag of
+// the policy, grid, block).
+template <class F>
+void by_addr(const gplbm_ctx* ctx, const F& f) {
+  const gplbm_params& p = ctx->p;
+  const int64_t plane = (int64_t)p.nx * p.ny;
+  // 32-bit byte offsets inside a plane of 8-byte values, z planes on the y
+  // axis of the grid
+  if (plane < ((int64_t)1 << 29) && p.nz <= 65535) {
+    const dim3 grid((unsigned)((plane + 255) / 256), p.nz, 1), block(256, 1, 1);
+    if (p.bc[0] || p.bc[1] || p.bc[2])
+      f(Tag<AddrPlane<true>>{}, grid, block);
+    else
+      f(Tag<AddrPlane<false>>{}, grid, block);
+  } else {
+    f(Tag<AddrGeneral>{}, dim3((p.nx + 63) / 64, (p.ny + 3) / 4, p.nz), dim3(64, 4, 1));
+  }
+}
+
 // Typed operations for the lattices L (g) and LH (h) and the storage /
 // arithmetic types S, C.
 template <class L, class LH, class S, class C>
@@ -258,17 +288,16 @@ struct Ops {
       const int a = ctx->cur, b = 1 - a;
       StepBufs<S> bufs{(const S*)ctx->G[a], (const S*)ctx->H[a], (const S*)ctx->PHI[a],
                        (S*)ctx->H[b],       (S*)ctx->PHI[b],       (S*)ctx->G[b]};
-      if (general(ctx)) {
-        hipLaunchKernelGGL((k_split_h<L, LH, S, C, true>), grid(ctx), block(), 0, ctx->stream, g, K,
-                           bufs);
-        hipLaunchKernelGGL((k_split_g<L, LH, S, C, true>), grid(ctx), block(), 0, ctx->stream, g, K,
-                           bufs);
-      } else {
-        hipLaunchKernelGGL((k_split_h<L, LH, S, C, false>), grid(ctx), block(), 0, ctx->stream, g,
-                           K, bufs);
-        hipLaunchKernelGGL((k_split_g<L, LH, S, C, false>), grid(ctx), block(), 0, ctx->stream, g,
-                           K, bufs);
-      }
+      by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+        using A = typename decltype(addr)::type;
+        if (general(ctx)) {
+          hipLaunchKernelGGL((k_split_h<L, LH, S, C, true, A>), gr, bl, 0, ctx->stream, g, K, bufs);
+          hipLaunchKernelGGL((k_split_g<L, LH, S, C, true, A>), gr, bl, 0, ctx->stream, g, K, bufs);
+        } else {
+          hipLaunchKernelGGL((k_split_h<L, LH, S, C, false, A>), gr, bl, 0, ctx->stream, g, K, bufs);
+          hipLaunchKernelGGL((k_split_g<L, LH, S, C, false, A>), gr, bl, 0, ctx->stream, g, K, bufs);
+        }
+      });
       int rc = check_launch(ctx, "split step");
       if (rc) return rc;
       ctx->cur = b;
@@ -348,7 +377,7 @@ struct DevOps {
     for (int64_t n = 0; n < nsteps; ++n) {
       const int a = ctx->cur, b = 1 - a;
       const DevStep st{state(ctx, a), state(ctx, b)};
-      if (ctx->sched == GPLBM_SCHED_FUSED) {
+      if (fused_steps(ctx)) {
         // the general instantiation only for h^eq,alt or eps_s != eps_l
         const bool gen = ctx->p.h_scheme != GPLBM_H_SOURCE || ctx->p.free_energy != GPLBM_FE_EQUAL;
         int rc;
@@ -360,8 +389,11 @@ struct DevOps {
                    : DevFused2D<Codec, L, LH, false>::launch(g, K, st, ctx->stream);
         if (rc) return fail(ctx, GPLBM_E_DEVICE, "fused step launch failed");
       } else {
-        hipLaunchKernelGGL((k_dev_split_h<Codec, L, LH>), grid(ctx), block(), 0, ctx->stream, g, K, st);
-        hipLaunchKernelGGL((k_dev_split_g<Codec, L, LH>), grid(ctx), block(), 0, ctx->stream, g, K, st);
+        by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+          using A = typename decltype(addr)::type;
+          hipLaunchKernelGGL((k_dev_split_h<Codec, L, LH, A>), gr, bl, 0, ctx->stream, g, K, st);
+          hipLaunchKernelGGL((k_dev_split_g<Codec, L, LH, A>), gr, bl, 0, ctx->stream, g, K, st);
+        });
       }
       int rc = check_launch(ctx, "step");
       if (rc) return rc;
@@ -454,8 +486,7 @@ struct InitFn<A, void, void, void> {
 template <class L, class LH, class S, class C>
 struct StepFn {
   static int run(gplbm_ctx* c, int64_t n) {
-    return c->sched == GPLBM_SCHED_FUSED ? Ops<L, LH, S, C>::step_fused(c, n)
-                                         : Ops<L, LH, S, C>::step_split(c, n);
+    return fused_steps(c) ? Ops<L, LH, S, C>::step_fused(c, n) : Ops<L, LH, S, C>::step_split(c, n);
   }
 };
 template <class A>
@@ -489,6 +520,25 @@ int choose_schedule(const gplbm_params& p) {
   if (p.schedule == GPLBM_SCHED_SPLIT) return GPLBM_SCHED_SPLIT;
   if (p.schedule == GPLBM_SCHED_FUSED) return fused_ok ? GPLBM_SCHED_FUSED : -1;
   return fused_ok ? GPLBM_SCHED_FUSED : GPLBM_SCHED_SPLIT;
+}
+
+// Whether the steps of an AUTO context on a fused 3-D grid run as the per-node
+// pair of kernels instead (the same bits).  A z-march takes at least four or
+// five planes of about 9 us however small the grid; the pair reads 1.5 times
+// the bytes, which costs little while they come from the last-level cache
+// (us per step, z-march / pair: 64^3 FP64 56 / 40, FP32 37 / 22, FP16 35 / 19;
+// 96^3 FP64 176 / 154, FP16 79 / 55; 128^3 FP32 162 / 180, FP16 131 / 133;
+// 200^3 FP16 624 / 520; 256^3 FP64 2350 / 2770, FP32 1170 / 1440, FP16 904 /
+// 982).  With walls the march's bounce bookkeeping moves the line up (256^3
+// FP32 1290 / 1430), and in the deviation formats the pair is the faster at
+// every size (256^3 FP16 1288 / 995, 512^3 9.5 / 9.0 ms).
+bool node_pair_faster(const gplbm_params& p) {
+  if (two_d(p.lattice)) return false;
+  const int64_t N = (int64_t)p.nx * p.ny * p.nz;
+  const bool walls = p.bc[0] || p.bc[1] || p.bc[2];
+  if (p.precision >= GPLBM_FP16_DEV) return walls || N <= 10000000;
+  if (walls) return N <= 4000000;
+  return N <= (p.precision == GPLBM_FP64 ? 2000000 : 1200000);
 }
 
 int use_device(gplbm_ctx* ctx) {
@@ -613,6 +663,7 @@ int gplbm_create(const gplbm_params* p, void* dev_buf, uint64_t bytes, void* str
   ctx->step = 0;
   ctx->ready = false;
   ctx->sched = sched;
+  ctx->node_steps = p->schedule == GPLBM_SCHED_AUTO && node_pair_faster(*p);
   ctx->stream = (hipStream_t)stream;
   if (hipGetDevice(&ctx->device) != hipSuccess) {
     delete ctx;

@@ -274,29 +274,56 @@ __global__ void __launch_bounds__(256) k_dev_init(Geo g, Coef<float> K,
 // ---------------------------------------------------------------------------
 // Split schedule in the deviation format (any boundaries).
 
-template <class Codec, class L, class LH>
+// Codes of the moving populations a node pulls from a distribution, and the
+// rest value, as one batch of loads; then the decoded values, given the
+// reference field on the node's stencil (own value for a bounced population).
+template <class L>
+struct DevPulls {
+  uint16_t code[L::Q];
+  float rest;
+  template <class A>
+  __device__ DevPulls(const A& a, const DevDist& d) : rest(d.rest[a.node()]) {
+#pragma unroll
+    for (int k = 0; k < L::Q; ++k)
+      code[k] = k == L::REST ? uint16_t(0)
+                             : *a.template source<L>((const uint16_t*)d.mov, k, L::Q - 1,
+                                                     [](int j) { return mslot<L>(j); });
+  }
+  template <class Codec, class A, class R>
+  __device__ float value(const A& a, const R& ref, int k) const {
+    if (k == L::REST) return rest;
+    const float in = ref(-L::ex[k], -L::ey[k], -L::ez[k]);
+    return dev_decode<Codec>(code[k],
+                             float(L::w[k]) * (a.template bounced<L>(k) ? ref(0, 0, 0) : in));
+  }
+};
+
+template <class Codec, class L, class LH, class Addr>
 __global__ void __launch_bounds__(256) k_dev_split_h(Geo g, Coef<float> K, DevStep b) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
+  const Stencil<L, float> st(ad, (const float*)b.cur.PHI);
+  const Stencil<LH, float> sl(ad, (const float*)b.cur.LAM);
+  const DevPulls<LH> ph(ad, b.cur.H);
+  const DevPulls<L> pg(ad, b.cur.G);
+  loads_issued();
   float h[LH::Q];
   double c = 0.0;
 #pragma unroll
   for (int k = 0; k < LH::Q; ++k) {
-    h[k] = pull_dev<Codec, LH>(g, b.cur.H, b.cur.LAM, k, x, y, z);
+    h[k] = ph.template value<Codec>(ad, sl, k);
     c = k == 0 ? double(h[k]) : c + double(h[k]);
   }
-  const float phi = b.cur.PHI[i];
+  const float phi = st(0, 0, 0);
   const float mu = float(closure(K.q, c, double(phi)));
   float gr[3], n[3];
-  gradient_normal<L, float>(DevGlobalPhi{g, b.cur.PHI, x, y, z}, K.eps2, gr, n);
+  gradient_normal<L, float>(st, K.eps2, gr, n);
   const float sbar = source_moment<float>(K, phi, mu);
   double sg = 0.0;
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) {
-    const double v = double(pull_dev<Codec, L>(g, b.cur.G, b.cur.PHI, k, x, y, z));
+    const double v = double(pg.template value<Codec>(ad, st, k));
     sg = k == 0 ? v : sg + v;
   }
   const float phin = float(sg + 0.5 * double(sbar));
@@ -314,35 +341,39 @@ __global__ void __launch_bounds__(256) k_dev_split_h(Geo g, Coef<float> K, DevSt
     if (k == LH::REST)
       b.nxt.H.rest[i] = hdec[k];
     else
-      b.nxt.H.mov[mov_index<LH>(g, k, x, y, z)] = enc[k];
+      b.nxt.H.mov[ad.slot(mslot<LH>(k), LH::Q - 1)] = enc[k];
   }
   b.nxt.LAM[i] = lam;
   b.nxt.PHI[i] = phin;
 }
 
-template <class Codec, class L, class LH>
+template <class Codec, class L, class LH, class Addr>
 __global__ void __launch_bounds__(256) k_dev_split_g(Geo g, Coef<float> K, DevStep b) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
+  // g decodes with phi^n, the gradient is that of phi^{n+1}
+  const Stencil<L, float> st(ad, (const float*)b.nxt.PHI), s0(ad, (const float*)b.cur.PHI);
+  const Stencil<LH, float> sl(ad, (const float*)b.nxt.LAM);
+  const DevPulls<LH> ph(ad, b.nxt.H);
+  const DevPulls<L> pg(ad, b.cur.G);
+  loads_issued();
   double c = 0.0;
 #pragma unroll
   for (int k = 0; k < LH::Q; ++k) {
-    const double v = double(pull_dev<Codec, LH>(g, b.nxt.H, b.nxt.LAM, k, x, y, z));
+    const double v = double(ph.template value<Codec>(ad, sl, k));
     c = k == 0 ? v : c + v;
   }
-  const float phi = b.nxt.PHI[i];
+  const float phi = st(0, 0, 0);
   const float mu = float(closure(K.q, c, double(phi)));
   float gr[3], n[3];
-  gradient_normal<L, float>(DevGlobalPhi{g, b.nxt.PHI, x, y, z}, K.eps2, gr, n);
+  gradient_normal<L, float>(st, K.eps2, gr, n);
   float G[L::Q], gs[L::Q];
   phi_sources<L, float>(K, phi, mu, n, G);
   double sg = 0.0;
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) {
-    const float gk = pull_dev<Codec, L>(g, b.cur.G, b.cur.PHI, k, x, y, z);
+    const float gk = pg.template value<Codec>(ad, s0, k);
     sg = k == 0 ? double(gk) : sg + double(gk);
     gs[k] = g_collide<L, float>(K, k, gk, phi, G[k]);
   }
@@ -355,7 +386,7 @@ __global__ void __launch_bounds__(256) k_dev_split_g(Geo g, Coef<float> K, DevSt
     if (k == L::REST)
       b.nxt.G.rest[i] = gdec[k];
     else
-      b.nxt.G.mov[mov_index<L>(g, k, x, y, z)] = enc[k];
+      b.nxt.G.mov[ad.slot(mslot<L>(k), L::Q - 1)] = enc[k];
   }
 }
 

@@ -45,36 +45,166 @@ struct GlobalPhi {
   }
 };
 
-template <class L, class LH, class S, class C, bool kGen>
+// Addressing of the per-node kernels.  AddrGeneral takes any grid, by the
+// rules of geometry.h.  AddrPlane serves grids whose population planes are
+// shorter than 4 GiB: threads run over the nodes of a z plane (blockIdx.y), so
+// a plane's base is a scalar and a neighbour a 32-bit offset wrapped once per
+// node, with no division or branch per population; with walls a bounced
+// population is a selected address.  Both give the same nodes.
+struct AddrGeneral {
+  const Geo& g;
+  int x, y, z;
+  __device__ AddrGeneral(const Geo& g_)
+      : g(g_), x(blockIdx.x * blockDim.x + threadIdx.x), y(blockIdx.y * blockDim.y + threadIdx.y),
+        z(blockIdx.z) {}
+  __device__ bool inside() const { return x < g.nx && y < g.ny; }
+  __device__ int64_t node() const { return node_index(g, x, y, z); }
+  // element of plane m among the q planes per z of a distribution
+  __device__ int64_t slot(int m, int q) const {
+    return ((int64_t)z * q + m) * ((int64_t)g.nx * g.ny) + (int64_t)y * g.nx + x;
+  }
+  template <class P>
+  __device__ bool bounced(int k) const {
+    int sx = x, sy = y, sz = z;
+    return !(pull_axis(sx, P::ex[k], g.nx, g.bcx) && pull_axis(sy, P::ey[k], g.ny, g.bcy) &&
+             pull_axis(sz, P::ez[k], g.nz, g.bcz));
+  }
+  template <class P, class S, class M>
+  __device__ const S* source(const S* f, int k, int q, const M& m) const {
+    int sx = x, sy = y, sz = z, kk = k;
+    if (!(pull_axis(sx, P::ex[k], g.nx, g.bcx) && pull_axis(sy, P::ey[k], g.ny, g.bcy) &&
+          pull_axis(sz, P::ez[k], g.nz, g.bcz)))
+      sx = x, sy = y, sz = z, kk = P::opp[k];
+    return f + ((int64_t)sz * q + m(kk)) * ((int64_t)g.nx * g.ny) + (int64_t)sy * g.nx + sx;
+  }
+  template <class P, class S>
+  __device__ S pull_pop(const S* __restrict__ f, int k) const { return pull<P>(g, f, k, x, y, z); }
+  template <class S>
+  __device__ S at(const S* __restrict__ f, int dx, int dy, int dz) const {
+    return f[node_index(g, stencil_axis(x + dx, g.nx, g.bcx), stencil_axis(y + dy, g.ny, g.bcy),
+                        stencil_axis(z + dz, g.nz, g.bcz))];
+  }
+};
+
+template <bool kWalls>
+struct AddrPlane {
+  int64_t plane;
+  bool in;
+  int zs[3], ps[3];    // planes z - 1, z, z + 1: wrapped, and with the mirror ghost
+  uint32_t src[3][3];  // in-plane offset of (x, y) + (c - 1, a - 1), wrapped, [a][c]
+  bool xm, xp, ym, yp, zm, zp;  // that neighbour lies beyond a wall
+
+  __device__ AddrPlane(const Geo& g) : plane((int64_t)g.nx * g.ny) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    in = i < (uint32_t)plane;
+    const int y = in ? i / (uint32_t)g.nx : 0, x = in ? i - y * g.nx : 0, z = blockIdx.y;
+    const int xo[3] = {x == 0 ? g.nx - 1 : x - 1, x, x == g.nx - 1 ? 0 : x + 1};
+    const int yo[3] = {y == 0 ? g.ny - 1 : y - 1, y, y == g.ny - 1 ? 0 : y + 1};
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) src[a][c] = (uint32_t)yo[a] * g.nx + xo[c];
+    zs[0] = z == 0 ? g.nz - 1 : z - 1;
+    zs[1] = z;
+    zs[2] = z == g.nz - 1 ? 0 : z + 1;
+    xm = kWalls && g.bcx && x == 0;
+    xp = kWalls && g.bcx && x == g.nx - 1;
+    ym = kWalls && g.bcy && y == 0;
+    yp = kWalls && g.bcy && y == g.ny - 1;
+    zm = kWalls && g.bcz && z == 0;
+    zp = kWalls && g.bcz && z == g.nz - 1;
+    ps[0] = zm ? z : zs[0];
+    ps[1] = z;
+    ps[2] = zp ? z : zs[2];
+  }
+  __device__ bool inside() const { return in; }
+  __device__ uint32_t self() const { return src[1][1]; }
+  __device__ int64_t node() const { return zs[1] * plane + self(); }
+  __device__ int64_t slot(int m, int q) const { return ((int64_t)zs[1] * q + m) * plane + self(); }
+  template <class P>
+  __device__ bool bounced(int k) const {
+    if (!kWalls) return false;
+    return (P::ex[k] > 0 && xm) || (P::ex[k] < 0 && xp) || (P::ey[k] > 0 && ym) ||
+           (P::ey[k] < 0 && yp) || (P::ez[k] > 0 && zm) || (P::ez[k] < 0 && zp);
+  }
+  // element of a plane at a 32-bit byte offset
+  template <class S>
+  __device__ static const S* elem(const S* base, uint32_t i) {
+    return reinterpret_cast<const S*>(reinterpret_cast<const char*>(base) + i * (uint32_t)sizeof(S));
+  }
+  // address of the value population k pulls, from a distribution of q planes
+  // per z with population j in plane m(j)
+  template <class P, class S, class M>
+  __device__ const S* source(const S* f, int k, int q, const M& m) const {
+    const S* p = elem(f + ((int64_t)zs[1 - P::ez[k]] * q + m(k)) * plane,
+                      src[1 - P::ey[k]][1 - P::ex[k]]);
+    if (kWalls && bounced<P>(k)) p = elem(f + ((int64_t)zs[1] * q + m(P::opp[k])) * plane, self());
+    return p;
+  }
+  template <class P, class S>
+  __device__ S pull_pop(const S* __restrict__ f, int k) const {
+    return *source<P>(f, k, P::Q, [](int j) { return j; });
+  }
+  // field at x + (dx, dy, dz), the mirror ghost at a wall
+  template <class S>
+  __device__ S at(const S* __restrict__ f, int dx, int dy, int dz) const {
+    uint32_t i = src[1 + dy][1 + dx];
+    if (kWalls) {
+      const int ox = (dx < 0 && xm) || (dx > 0 && xp) ? 0 : dx;
+      const int oy = (dy < 0 && ym) || (dy > 0 && yp) ? 0 : dy;
+      const uint32_t row = oy < 0 ? src[0][1] : (oy > 0 ? src[2][1] : src[1][1]);
+      const int step = ox < 0 ? (int)(src[1][0] - src[1][1]) : (ox > 0 ? (int)(src[1][2] - src[1][1]) : 0);
+      i = row + step;
+    }
+    return *elem(f + ps[1 + dz] * plane, i);
+  }
+};
+
+// Values of a field at the nodes the gradient stencil of lattice L reads, all
+// loaded at once.
+template <class L, class C>
+struct Stencil {
+  C v[3][3][3];
+  template <class A, class S>
+  __device__ Stencil(const A& a, const S* __restrict__ f) {
+#pragma unroll
+    for (int k = 0; k < L::Q; ++k)
+      v[1 + L::ez[k]][1 + L::ey[k]][1 + L::ex[k]] = C(a.at(f, L::ex[k], L::ey[k], L::ez[k]));
+  }
+  __device__ C operator()(int dx, int dy, int dz) const { return v[1 + dz][1 + dy][1 + dx]; }
+};
+
+// The loads of a node stay one batch: the scheduler does not move arithmetic
+// between them.
+__device__ __forceinline__ void loads_issued() { __builtin_amdgcn_sched_barrier(0); }
+
+template <class L, class LH, class S, class C, bool kGen, class Addr>
 __global__ void __launch_bounds__(256) k_split_h(Geo g, Coef<C> Kin, StepBufs<S> b) {
   const Coef<C> K = variant<kGen>(Kin);
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
 
-  C h[LH::Q];
+  S h[LH::Q], gv[L::Q];
+  const Stencil<L, C> st(ad, b.PHI);
+#pragma unroll
+  for (int k = 0; k < LH::Q; ++k) h[k] = ad.template pull_pop<LH>(b.H, k);
+#pragma unroll
+  for (int k = 0; k < L::Q; ++k) gv[k] = ad.template pull_pop<L>(b.G, k);
+  loads_issued();
   double c = 0.0;
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) {
-    S v = pull<LH>(g, b.H, k, x, y, z);
-    h[k] = C(v);
-    c = k == 0 ? double(v) : c + double(v);
-  }
-  const C phi = C(b.PHI[i]);
+  for (int k = 0; k < LH::Q; ++k) c = k == 0 ? double(h[k]) : c + double(h[k]);
+  const C phi = st(0, 0, 0);
   const double mu_d = closure(K.q, c, double(phi));
   const C mu = C(mu_d);
   C gr[3], n[3];
-  gradient_normal<L, C>(GlobalPhi<S, C>{g, b.PHI, x, y, z}, K.eps2, gr, n);
+  gradient_normal<L, C>(st, K.eps2, gr, n);
   const C sbar = source_moment<C>(K, phi, mu);
 
   double sg = 0.0;
 #pragma unroll
-  for (int k = 0; k < L::Q; ++k) {
-    double v = double(pull<L>(g, b.G, k, x, y, z));
-    sg = k == 0 ? v : sg + v;
-  }
+  for (int k = 0; k < L::Q; ++k) sg = k == 0 ? double(gv[k]) : sg + double(gv[k]);
   const double phin = sg + 0.5 * double(sbar);
   const C dtphi = C(phin) - phi;
 
@@ -86,42 +216,42 @@ __global__ void __launch_bounds__(256) k_split_h(Geo g, Coef<C> Kin, StepBufs<S>
   h_update<LH>(K, h, cc, lam, F, hs);
   balance_rest<LH, S, C>(hs, c);
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) b.Hn[pop_index<LH>(g, k, x, y, z)] = S(hs[k]);
+  for (int k = 0; k < LH::Q; ++k) b.Hn[ad.slot(k, LH::Q)] = S(hs[k]);
   b.PHIn[i] = S(phin);
 }
 
-template <class L, class LH, class S, class C, bool kGen>
+template <class L, class LH, class S, class C, bool kGen, class Addr>
 __global__ void __launch_bounds__(256) k_split_g(Geo g, Coef<C> Kin, StepBufs<S> b) {
   const Coef<C> K = variant<kGen>(Kin);
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
+  const Addr ad(g);
+  if (!ad.inside()) return;
 
+  S hv[LH::Q], gv[L::Q];
+  const Stencil<L, C> st(ad, (const S*)b.PHIn);
+#pragma unroll
+  for (int k = 0; k < LH::Q; ++k) hv[k] = ad.template pull_pop<LH>((const S*)b.Hn, k);
+#pragma unroll
+  for (int k = 0; k < L::Q; ++k) gv[k] = ad.template pull_pop<L>(b.G, k);
+  loads_issued();
   double c = 0.0;
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) {
-    double v = double(pull<LH>(g, (const S*)b.Hn, k, x, y, z));
-    c = k == 0 ? v : c + v;
-  }
-  const C phi = C(b.PHIn[i]);
+  for (int k = 0; k < LH::Q; ++k) c = k == 0 ? double(hv[k]) : c + double(hv[k]);
+  const C phi = st(0, 0, 0);
   const C mu = C(closure(K.q, c, double(phi)));
   C gr[3], n[3];
-  gradient_normal<L, C>(GlobalPhi<S, C>{g, b.PHIn, x, y, z}, K.eps2, gr, n);
+  gradient_normal<L, C>(st, K.eps2, gr, n);
   C G[L::Q];
   phi_sources<L, C>(K, phi, mu, n, G);
   C gs[L::Q];
   double sg = 0.0;
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) {
-    const S v = pull<L>(g, b.G, k, x, y, z);
-    sg = k == 0 ? double(v) : sg + double(v);
-    gs[k] = C(S(g_collide<L, C>(K, k, C(v), phi, G[k])));
+    sg = k == 0 ? double(gv[k]) : sg + double(gv[k]);
+    gs[k] = C(S(g_collide<L, C>(K, k, C(gv[k]), phi, G[k])));
   }
   balance_g_rest<L, S, C>(K, gs, sg, phi, source_moment<C>(K, phi, mu));
 #pragma unroll
-  for (int k = 0; k < L::Q; ++k) b.Gn[pop_index<L>(g, k, x, y, z)] = S(gs[k]);
+  for (int k = 0; k < L::Q; ++k) b.Gn[ad.slot(k, L::Q)] = S(gs[k]);
 }
 
 // ---------------------------------------------------------------------------
