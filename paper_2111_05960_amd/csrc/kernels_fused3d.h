@@ -9,18 +9,16 @@
 //   - takes phi^n of planes p-1, p, p+1 from a 3-plane LDS ring (T+2 in x-y)
 //     for the gradient, writes phi^{n+1}(p) into a second ring,
 //   - runs the h collision of step n.
-// The post-collision h* are then streamed inside the block, to three planes:
-// the e_z = +1 populations to plane p+1, the in-plane ones to plane p, the
-// e_z = -1 ones to plane p-1.  Where the g carry is in registers the h* go to
-// an LDS exchange and every node gathers its own contributions from x - e_k
-// into three rolling partial sums (one barrier); with the LDS g carry they
-// are pushed into a ring of three LDS accumulator planes in ordered passes.
-// Because D3Q19 and D3Q7 are numbered by layers of e_z (+1, 0, -1), every
-// node's c^{n+1} receives its populations in index order across the three
-// planes either way, the order of a pull.
+// The post-collision h* are then streamed inside the block: they go to an LDS
+// exchange, and after one barrier every node gathers its own contributions
+// from x - e_k into three rolling partial sums (the e_z = +1 populations reach
+// plane p+1, the in-plane ones plane p, the e_z = -1 ones plane p-1).  Because
+// D3Q19 and D3Q7 are numbered by layers of e_z (+1, 0, -1), every node's
+// c^{n+1} receives its populations in index order across the three planes, the
+// order of a pull.
 // After plane p, c^{n+1}(p-1) is complete and the threads of T run the g
 // collision of step n+1 at plane p-1, on the g~^{n+1} pulled one plane
-// earlier (kept in registers, or in LDS where registers are short).
+// earlier (kept in registers, or in the LDS, every thread in slots of its own).
 //
 // Tiles are x-aligned with the halo columns in extra lanes, and the grid is
 // persistent with XCD-ordered passes (tiles.h): every output row is whole
@@ -45,6 +43,8 @@
 // values from the node's own entries there; past a top wall a closing plane
 // finishes the last one.
 #pragma once
+
+#include <type_traits>
 
 #include "kernels_fused2d.h"
 #include "tiles.h"
@@ -85,27 +85,47 @@ __device__ __forceinline__ void bstore_nt(S v, __amdgpu_buffer_rsrc_t r, uint32_
   }
 }
 
-// Pulls of the populations of lattice P at z plane zp: population k comes
-// from plane group zp - e_z and (x, y) - (e_x, e_y), whose byte offset inside
-// a population plane is xyb[1 - e_y][1 - e_x].
-template <class P, class S>
-__device__ __forceinline__ void fetch_pops(const S* base, int zp, int nz, int plane,
-                                           const uint32_t (&xyb)[3][3], S (&v)[P::Q]) {
+// Pulls of the populations of lattice P at plane p: population k comes from
+// plane group p - e_z and (x, y) - (e_x, e_y), whose byte offset inside a
+// population plane is xyb[1 - e_y][1 - e_x].  With walls bounced populations
+// (bits of `bounce` for the x and y walls, whole e_z layers at a z wall) are
+// the node's own opposite ones; a wavefront without any takes the plain pulls.
+template <class P, class S, bool kWalls>
+__device__ __forceinline__ void fetch(const S* base, int p, int nz, bool wz, int plane,
+                                      const uint32_t (&xyb)[3][3], uint32_t bounce, S (&v)[P::Q]) {
   const int64_t groupB = int64_t(plane) * P::Q * sizeof(S);
   const uint32_t planeB = uint32_t(plane) * sizeof(S);
-  const int zs[3] = {(zp == 0 ? nz - 1 : zp - 1), zp, (zp == nz - 1 ? 0 : zp + 1)};
+  const int zp = wz ? min(p, nz - 1) : wrap_coord(p, nz);
+  const int zs[3] = {wz ? max(zp - 1, 0) : (zp == 0 ? nz - 1 : zp - 1), zp,
+                     wz ? min(zp + 1, nz - 1) : (zp == nz - 1 ? 0 : zp + 1)};
   __amdgpu_buffer_rsrc_t R[3];
 #pragma unroll
   for (int j = 0; j < 3; ++j)
     R[j] = make_rsrc(reinterpret_cast<const char*>(base) + zs[j] * groupB, uint32_t(groupB));
+  if constexpr (kWalls) {
+    uint32_t m = bounce;
+    if (wz && p == 0) m |= ez_mask<P>(1);
+    if (wz && p == nz - 1) m |= ez_mask<P>(-1);
+    if (__builtin_amdgcn_ballot_w64(m != 0u) != 0u) {
+#pragma unroll
+      for (int k = 0; k < P::Q; ++k) {
+        if ((m >> k) & 1u)
+          v[k] = bload<S>(R[1], xyb[1][1], P::opp[k] * planeB);
+        else
+          v[k] = bload<S>(R[1 - P::ez[k]], xyb[1 - P::ey[k]][1 - P::ex[k]], k * planeB);
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int k = 0; k < P::Q; ++k)
     v[k] = bload<S>(R[1 - P::ez[k]], xyb[1 - P::ey[k]][1 - P::ex[k]], k * planeB);
 }
 
 // Carry of the pulled g~^{n+1} from its plane to the collision one plane
-// later: in registers, or in two LDS buffers (by plane parity) written right
-// after the pull, which frees 2Q registers in FP64.
+// later: in registers, or in the LDS, in slots that only their own thread
+// touches.  The pulls of plane p wait in registers until the collision of
+// plane p - 1 has read the slots, so one buffer does.
 enum class Carry { kRegisters, kLds };
 
 // Zero-flux walls in the z-marching kernels.  A population whose source
@@ -134,48 +154,65 @@ __device__ __forceinline__ uint32_t xy_bounce_mask(const Geo& g, int ux, int uy)
 }
 
 
-template <class L, class S>
+// Which pulls of the next plane are issued while a plane is computed (into
+// registers; with any of them also the phi^n tile of the plane after next).
+enum class Prefetch { kNone, kH, kBoth };
+
+// Tile height, longest z chunk, carry and prefetch, measured on the 512^3 and
+// 256^3 (or 320^3) steps in ms against the form before (g carried in two
+// buffers by plane parity and h* pushed in ordered passes in FP64, else g
+// carried in registers, no prefetch of the pulls):
+//   D3Q19 FP64  18.5-19.0 against 19.8-20.1 (2.35 against 2.53); the LDS is
+//               full (163392 of 163840 bytes); a prefetch of h spills and one
+//               of both on 5 rows loses the neighbours' lines from the L2
+//               (21.0 and 21.9)
+//   D3Q19 FP32  8.90 against 9.86 (1.17 against 1.29); both prefetched 9.25,
+//               13 rows 10.4, 11 and 10 rows 8.96
+//   h on D3Q7   320^3 FP64 2.94 on 8 rows against 3.62 on 6; FP32 1.58 on 13
+//               rows against 1.78 on 12
+//   D3Q7 FP64   320^3 1.56 against 1.75; 512^3 6.72 against 6.91
+//   D3Q7 FP32   320^3 0.863 on 12 rows, 0.895 on 8, against 1.00; 512^3 3.59
+//               against 3.99
+template <class L, class LH, class S>
 struct Fused3DConfig;
-// 32-plane z chunks: 11008 tiles at 512^3, 43 passes of the 256 resident
-// blocks; 64-plane chunks (two halo planes per 66 instead of per 34) ran
-// level in the plain FP64 step (20.06-20.26 against 20.20-20.24 ms) and 3%
-// slower in its general instantiation (h^eq,alt 22.1 against 21.3-21.5)
 template <>
-struct Fused3DConfig<D3Q19, double> {
+struct Fused3DConfig<D3Q19, D3Q19, double> {
   static constexpr int TX = 64, TY = 6, ZC = 32;
   static constexpr Carry carry = Carry::kLds;
-  static constexpr bool prefetch = false;
+  static constexpr Prefetch prefetch = Prefetch::kNone;
 };
-// FP32: the phi^n tile of the plane after next is fetched into registers
-// while a plane is computed (512^3: 9.65-10.0 against 10.6-10.8 ms per step,
-// with h on D3Q7 7.28 against 7.52; in FP64 it ran 2% slower, on D3Q7 12%
-// slower in FP32 and level in FP64); 64-plane z chunks (9.86-9.92 against
-// 9.97-10.01 ms with 32; 2752 tiles at 512^3, 10.75 passes)
 template <>
-struct Fused3DConfig<D3Q19, float> {
+struct Fused3DConfig<D3Q19, D3Q19, float> {
   static constexpr int TX = 64, TY = 12, ZC = 64;
-  static constexpr Carry carry = Carry::kRegisters;
-  static constexpr bool prefetch = true;
+  static constexpr Carry carry = Carry::kLds;
+  static constexpr Prefetch prefetch = Prefetch::kH;
 };
-// g on D3Q7: 7 populations carried in registers; tile heights measured on
-// the 512^3 step (FP64: 12 rows 7.05 ms, 8 rows 7.79, 6 rows 8.36; FP32: 8
-// rows 4.05 ms, 12 rows 4.40, 6 rows 4.18); FP32 in 64-plane z chunks (4096
-// tiles at 512^3, 16 passes of the 256 resident blocks: 3.97-3.98 against
-// 4.05 ms with 32, with walls 5.17 against 5.29; FP64 gained 0.5%)
 template <>
-struct Fused3DConfig<D3Q7, double> {
+struct Fused3DConfig<D3Q19, D3Q7, double> {
+  static constexpr int TX = 64, TY = 8, ZC = 32;
+  static constexpr Carry carry = Carry::kLds;
+  static constexpr Prefetch prefetch = Prefetch::kH;
+};
+template <>
+struct Fused3DConfig<D3Q19, D3Q7, float> {
+  static constexpr int TX = 64, TY = 13, ZC = 64;
+  static constexpr Carry carry = Carry::kLds;
+  static constexpr Prefetch prefetch = Prefetch::kH;
+};
+template <>
+struct Fused3DConfig<D3Q7, D3Q7, double> {
   static constexpr int TX = 64, TY = 12, ZC = 32;
   static constexpr Carry carry = Carry::kRegisters;
-  static constexpr bool prefetch = false;
+  static constexpr Prefetch prefetch = Prefetch::kH;
 };
 template <>
-struct Fused3DConfig<D3Q7, float> {
-  static constexpr int TX = 64, TY = 8, ZC = 64;
+struct Fused3DConfig<D3Q7, D3Q7, float> {
+  static constexpr int TX = 64, TY = 12, ZC = 64;
   static constexpr Carry carry = Carry::kRegisters;
-  static constexpr bool prefetch = false;
+  static constexpr Prefetch prefetch = Prefetch::kH;
 };
 
-template <int TX, int TY, Carry kCarryMode, bool kPrefetch, class L, class LH, class S, class C,
+template <int TX, int TY, Carry kCarryMode, Prefetch kPF, class L, class LH, class S, class C,
           bool kGen, bool kWalls>
 __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     k_fused3d(Geo g, Coef<C> Kin, StepBufs<S> b, int tiles_x, int tiles_xy, int ntiles, int zc) {
@@ -184,35 +221,29 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
   constexpr int Q = L::Q, QH = LH::Q;
   // e_z layers of the h lattice: +1 at [0, NU), 0 at [NU, NU+NM), -1 after
   constexpr int NU = count_ez<LH>(1), NM = count_ez<LH>(0), ND = count_ez<LH>(-1);
-  constexpr int NPASS = NM > NU ? (NM > ND ? NM : ND) : (NU > ND ? NU : ND);
   static_assert(NU + NM + ND == QH, "h lattice must be numbered by layers of e_z");
+  static_assert(LH::REST == NU, "the rest vector opens the in-plane layer");
   constexpr int BX = Shape::BX, BY = Shape::BY;
   constexpr int AX = BX + 2, AY = BY + 2;
   constexpr int NT = Shape::NT;
   constexpr int PHI_PER_THREAD = (AX * AY + NT - 1) / NT;
   constexpr bool kRegs = kCarryMode == Carry::kRegisters;
-  // In-block streaming of h*: with the register carry of g the LDS has room
-  // for an exchange of the post-collision h* of the plane, which the readers
-  // gather from after one barrier, keeping their partial sums of c^{n+1} in
-  // registers (g and h on D3Q19 in FP32 spills 8-11 VGPRs doing so and is
-  // still faster, 10.0 against 10.6 ms at 512^3); with the LDS carry (FP64
-  // D3Q19) they are pushed into an accumulator ring in NPASS ordered passes.
-  // Both sum every c^{n+1} in population order.
-  constexpr bool kGather = kRegs;
-  static_assert(!kWalls || kGather, "walls need the gather form");
+  constexpr bool kPrefetch = kPF != Prefetch::kNone, kPrefetchG = kPF == Prefetch::kBoth;
   __shared__ C phiA[3][AY][AX];  // phi^n, planes p-1, p, p+1
   __shared__ C phiB[3][BY][BX];  // phi^{n+1}, planes p-2, p-1, p
-  // c^{n+1} being accumulated (push passes)
-  __shared__ double acc[kGather ? 1 : 3][kGather ? 1 : BY][kGather ? 1 : BX];
-  // h* of plane p, moving populations (gather)
-  __shared__ C hx[kGather ? QH : 1][kGather ? BY : 1][kGather ? BX : 1];
-  // With walls the e_z = +1 layer of the exchange is kept for one more plane
-  // (by plane parity): the plane above gathers it after its own barrier, and
-  // a node's own values in it are the bounce of its e_z = -1 populations.
-  // The plane's two barriers order the reuse of a parity buffer.
+  // Moving h* of plane p (the readers gather from x - e_k after one barrier):
+  // slots 0 .. NX-1; with walls the e_z = +1 layer is in hxu instead, kept for
+  // one more plane (by plane parity): the plane above gathers it after its own
+  // barrier, and a node's own values in it are the bounce of its e_z = -1
+  // populations.  The plane's two barriers order the reuse of a parity buffer.
+  constexpr int NX = kWalls ? QH - 1 - NU : QH - 1;
+  __shared__ C hx[NX][BY][BX];
   __shared__ C hxu[kWalls ? 2 : 1][kWalls ? NU : 1][kWalls ? BY : 1][kWalls ? BX : 1];
-  // pulled g~^{n+1} of the output nodes by plane parity (LDS carry)
-  __shared__ C gkeep[kRegs ? 1 : 2][kRegs ? 1 : Q][kRegs ? 1 : TY][kRegs ? 1 : TX];
+  // g~^{n+1} of the output nodes, pulled at plane p - 1 (LDS carry): every
+  // thread reads and writes its own slots only, so no barrier orders them
+  __shared__ C gkeep[kRegs ? 1 : Q][kRegs ? 1 : TY][kRegs ? 1 : TX];
+  // slot of moving population k in hx
+  auto xslot = [](int k) constexpr { return kWalls ? k - NU - 1 : (k < LH::REST ? k : k - 1); };
 
   int tx, ty;
   bool valid;
@@ -230,13 +261,14 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     const int z0 = chunk * zc, z1 = min(z0 + zc, nz);
 
     const int ux = X0 - 1 + tx, uy = Y0 - 1 + ty;
-    const bool out = valid && ux < nx && uy < ny && tx >= 1 && tx <= TX && ty >= 1 && ty <= TY;
+    const bool inner = valid && tx >= 1 && tx <= TX && ty >= 1 && ty <= TY;
+    const bool out = inner && ux < nx && uy < ny;
     // region nodes beyond a wall take no part (with walls only)
     bool active = valid;
     if constexpr (kWalls)
       active = valid && (!g.bcx || (ux >= 0 && ux < nx)) && (!g.bcy || (uy >= 0 && uy < ny));
-    const int x = kWalls ? tile_coord(ux, nx, g.bcx) : wrap_coord(ux, nx);
-    const int y = kWalls ? tile_coord(uy, ny, g.bcy) : wrap_coord(uy, ny);
+    const int x = kWalls ? tile_coord(ux, nx, g.bcx) : wrap_near(ux, nx);
+    const int y = kWalls ? tile_coord(uy, ny, g.bcy) : wrap_near(uy, ny);
     // source offsets wrap also on wall axes: a source beyond a wall is never
     // read (its population bounces), the wrapped address keeps it in range
     const int xo[3] = {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1};
@@ -266,8 +298,8 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
 #pragma unroll
     for (int j = 0; j < PHI_PER_THREAD; ++j) {
       const int l = min((int)threadIdx.x + j * NT, AX * AY - 1);
-      const int gx = kWalls ? tile_coord(X0 - 2 + l % AX, nx, g.bcx) : wrap_coord(X0 - 2 + l % AX, nx);
-      const int gy = kWalls ? tile_coord(Y0 - 2 + l / AX, ny, g.bcy) : wrap_coord(Y0 - 2 + l / AX, ny);
+      const int gx = kWalls ? tile_coord(X0 - 2 + l % AX, nx, g.bcx) : wrap_near(X0 - 2 + l % AX, nx);
+      const int gy = kWalls ? tile_coord(Y0 - 2 + l / AX, ny, g.bcy) : wrap_near(Y0 - 2 + l / AX, ny);
       phi_off[j] = uint32_t(gy * nx + gx);
     }
     auto fetch_phi = [&](int p, S (&v)[PHI_PER_THREAD]) {
@@ -283,104 +315,63 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
         if (l < AX * AY) phiA[ring3(p)][l / AX][l % AX] = C(v[j]);
       }
     };
-    auto load_phi = [&](int p) {
-      S v[PHI_PER_THREAD];
-      fetch_phi(p, v);
-      put_phi(p, v);
+    // pulls of plane p (h or g); a source beyond a wall gives the node's own
+    // opposite population (bounce-back); a plane beyond a z wall is never read
+    auto fetch_h = [&](int p, S (&v)[QH]) {
+      fetch<LH, S, kWalls>(b.H, p, nz, wz, plane, xyb, bmh, v);
+    };
+    auto fetch_g = [&](int p, S (&v)[Q]) {
+      fetch<L, S, kWalls>(b.G, p, nz, wz, plane, xyb, bmg, v);
     };
     // first plane: the halo plane below the chunk, or the bottom plane at a
     // z wall
     const int pfirst = (wz && z0 == 0) ? 0 : z0 - 1;
-    load_phi(pfirst - 1);
-    load_phi(pfirst);
+    S hv[QH], gv[Q], phi_next[PHI_PER_THREAD];
+    {
+      S v0[PHI_PER_THREAD], v1[PHI_PER_THREAD];
+      fetch_phi(pfirst - 1, v0);
+      fetch_phi(pfirst, v1);
+      if constexpr (kPrefetch) {
+        fetch_phi(pfirst + 1, phi_next);
+        fetch_h(pfirst, hv);
+        if constexpr (kPrefetchG) fetch_g(pfirst, gv);
+      }
+      put_phi(pfirst - 1, v0);
+      put_phi(pfirst, v1);
+    }
     C g_old[kRegs ? Q : 1];
 #pragma unroll
     for (int k = 0; k < (kRegs ? Q : 1); ++k) g_old[k] = C(0);
-    // gather: c^{n+1} of this thread's node on planes p-1 and p, partly
-    // summed (the e_z = +1 populations arrive one plane early, the e_z = -1
-    // ones one plane late, each layer in ascending k)
-    const bool inner = valid && tx >= 1 && tx <= TX && ty >= 1 && ty <= TY;
+    // c^{n+1} of this thread's node on planes p-1 and p, partly summed (the
+    // e_z = +1 populations arrive one plane early, the e_z = -1 ones one plane
+    // late, each layer in ascending k)
     double acc_dn = 0.0, acc_mid = 0.0;
     double sg_old = 0.0;
-
-    // prefetch: the phi^n tile of the plane after next, in flight in
-    // registers while the current plane is computed
-    S phi_next[kPrefetch ? PHI_PER_THREAD : 1];
-    if constexpr (kPrefetch) fetch_phi(pfirst + 1, phi_next);
 
     for (int p = pfirst; p <= z1; ++p) {
       // past a top wall: no plane, only the completion of plane nz - 1
       const bool closing = wz && p == nz;
       const bool work = !kWalls || (active && !closing);
+      if constexpr (!kPrefetch) fetch_phi(p + 1, phi_next);
+      put_phi(p + 1, phi_next);
       if constexpr (kPrefetch) {
-        put_phi(p + 1, phi_next);
-        fetch_phi(p + 2, phi_next);
-      } else {
-        load_phi(p + 1);
+        if (p < z1) fetch_phi(p + 2, phi_next);
       }
       __syncthreads();
       const int zp = wz ? min(p, nz - 1) : wrap_coord(p, nz);
-      // all e_z = +1 (-1) sources of this plane lie beyond the bottom (top) wall
+      // all e_z = +1 sources of this plane lie beyond the bottom wall
       const bool bz_up = wz && p == 0;
       const int sA = ring3(p);
       const bool own_p = p >= z0 && p < z1;
+      if constexpr (!kPrefetch) fetch_h(p, hv);
+      if constexpr (!kPrefetchG) fetch_g(p, gv);
 
       C hs[QH];
-      C g_new[kRegs ? Q : 1];
       double sg = 0.0;
       if (work) {
-        S hv[QH], gv[Q];
-        if constexpr (!kWalls) {
-          fetch_pops<LH, S>(b.H, zp, nz, plane, xyb, hv);
-          fetch_pops<L, S>(b.G, zp, nz, plane, xyb, gv);
-        } else {
-          // pulls; a source beyond a wall gives the node's own opposite
-          // population (bounce-back); a plane beyond a z wall is never read
-          const bool bz_dn = wz && p == nz - 1;
-          const int zs[3] = {wz ? max(zp - 1, 0) : (zp == 0 ? nz - 1 : zp - 1), zp,
-                             wz ? min(zp + 1, nz - 1) : (zp == nz - 1 ? 0 : zp + 1)};
-          __amdgpu_buffer_rsrc_t RH[3], RG[3];
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            RH[j] = make_rsrc(reinterpret_cast<const char*>(b.H) + zs[j] * groupH, uint32_t(groupH));
-            RG[j] = make_rsrc(reinterpret_cast<const char*>(b.G) + zs[j] * groupB, uint32_t(groupB));
-          }
-#pragma unroll
-          for (int k = 0; k < QH; ++k) {
-            const bool bz = (LH::ez[k] > 0 && bz_up) || (LH::ez[k] < 0 && bz_dn);
-            if (bz || ((bmh >> k) & 1u))
-              hv[k] = bload<S>(RH[1], selfB, LH::opp[k] * planeB);
-            else
-              hv[k] = bload<S>(RH[1 - LH::ez[k]], xyb[1 - LH::ey[k]][1 - LH::ex[k]], k * planeB);
-          }
-#pragma unroll
-          for (int k = 0; k < Q; ++k) {
-            const bool bz = (L::ez[k] > 0 && bz_up) || (L::ez[k] < 0 && bz_dn);
-            if (bz || ((bmg >> k) & 1u))
-              gv[k] = bload<S>(RG[1], selfB, L::opp[k] * planeB);
-            else
-              gv[k] = bload<S>(RG[1 - L::ez[k]], xyb[1 - L::ey[k]][1 - L::ex[k]], k * planeB);
-          }
-        }
-
-        C h[QH];
         double c = 0.0;
 #pragma unroll
-        for (int k = 0; k < QH; ++k) {
-          h[k] = C(hv[k]);
-          c = k == 0 ? double(hv[k]) : c + double(hv[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < Q; ++k) {
-          if constexpr (kRegs) g_new[k] = C(gv[k]);
-          sg = k == 0 ? double(gv[k]) : sg + double(gv[k]);
-        }
-        if constexpr (!kRegs) {
-          if (out && own_p) {
-#pragma unroll
-            for (int k = 0; k < Q; ++k) gkeep[p & 1][k][ty - 1][tx - 1] = C(gv[k]);
-          }
-        }
+        for (int k = 0; k < QH; ++k) c = k == 0 ? double(hv[k]) : c + double(hv[k]);
         const C phi = phiA[sA][ty + 1][tx + 1];
         const C mu = C(closure(K.q, c, double(phi)));
         auto atA = [&](int dx, int dy, int dz) -> C {
@@ -389,6 +380,8 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
         C gr[3], n[3];
         gradient_normal<L, C>(atA, K.eps2, gr, n);
         const C sbar = source_moment<C>(K, phi, mu);
+#pragma unroll
+        for (int k = 0; k < Q; ++k) sg = k == 0 ? double(gv[k]) : sg + double(gv[k]);
         const double phin = sg + 0.5 * double(sbar);
         const C phin_c = C(phin);
         if (active) phiB[sA][ty][tx] = phin_c;
@@ -397,33 +390,40 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
         h_flux<L, C>(K, mu, gr, n, dtphi, K.anti_trapping != 0, F);
         const C lam = h_lambda<C>(K, phi, mu);
         const C cc = C(c);
-        h_update<LH>(K, h, cc, lam, F, hs);
+        h_update<LH>(K, hv, cc, lam, F, hs);
         balance_rest<LH, S, C>(hs, c);
-
-        if (out && own_p) {
-          const auto Hw = make_rsrc(reinterpret_cast<char*>(b.Hn) + zp * groupH, uint32_t(groupH));
+        if (active) {
 #pragma unroll
-          for (int k = 0; k < QH; ++k) bstore_nt<S>(S(hs[k]), Hw, selfB, k * planeB);
-          __builtin_nontemporal_store(S(phin_c), &b.PHIn[(int64_t)zp * plane + y * nx + x]);
+          for (int k = 0; k < QH; ++k) {
+            if (k == LH::REST) continue;
+            if (kWalls && k < NU)
+              hxu[kWalls ? p & 1 : 0][kWalls ? k : 0][ty][tx] = hs[k];
+            else
+              hx[xslot(k)][ty][tx] = hs[k];
+          }
         }
       }
-
-      const bool up_ok = p + 1 >= z0 && p + 1 < z1, dn_ok = p - 1 >= z0 && p - 1 < z1;
-      double acc_up = 0.0;
-      if constexpr (kGather && !kWalls) {
-        // every region node publishes its moving h*, then each inner node
-        // gathers from x - e_k in population order
-        if (valid) {
+      if (work && out && own_p) {
+        const auto Hw = make_rsrc(reinterpret_cast<char*>(b.Hn) + zp * groupH, uint32_t(groupH));
 #pragma unroll
-          for (int k = 0; k < QH; ++k)
-            if (k != LH::REST) hx[k][ty][tx] = hs[k];
-        }
-        __syncthreads();
+        for (int k = 0; k < QH; ++k) bstore_nt<S>(S(hs[k]), Hw, selfB, k * planeB);
+        __builtin_nontemporal_store(S(phiB[sA][ty][tx]), &b.PHIn[(int64_t)zp * plane + y * nx + x]);
+      }
+      // after the h stores: the wait for these pulls then waits for no store
+      // issued later
+      if constexpr (kPrefetch) {
+        if (p < z1) fetch_h(p + 1, hv);
+      }
+
+      __syncthreads();
+      const bool dn_ok = p - 1 >= z0 && p - 1 < z1;
+      double acc_up = 0.0;
+      if constexpr (!kWalls) {
         if (inner) {
 #pragma unroll
           for (int k = 0; k < QH; ++k) {
             const double v = k == LH::REST ? double(hs[k])
-                                           : double(hx[k][ty - LH::ey[k]][tx - LH::ex[k]]);
+                                           : double(hx[xslot(k)][ty - LH::ey[k]][tx - LH::ex[k]]);
             if (LH::ez[k] > 0)
               acc_up = k == 0 ? v : acc_up + v;
             else if (LH::ez[k] == 0)
@@ -432,24 +432,12 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
               acc_dn = acc_dn + v;
           }
         }
-      }
-      if constexpr (kWalls) {
-        // the e_z = +1 layer goes to the parity buffer of plane p, the others
-        // to the exchange; then the node's c^{n+1}(p) through its in-plane
-        // layer (the e_z = +1 layer from plane p - 1, or bounced) and the
-        // e_z = -1 layer of c^{n+1}(p - 1) (from plane p, or bounced: the
-        // node's own e_z = +1 values of plane p - 1), each in population order
-        const int ub = p & 1, pb = ub ^ 1;
-        if (active && !closing) {
-#pragma unroll
-          for (int k = 0; k < QH; ++k) {
-            if (k < NU)
-              hxu[ub][k][ty][tx] = hs[k];
-            else if (k != LH::REST)
-              hx[k][ty][tx] = hs[k];
-          }
-        }
-        __syncthreads();
+      } else {
+        // the node's c^{n+1}(p) through its in-plane layer (the e_z = +1 layer
+        // from plane p - 1, or bounced) and the e_z = -1 layer of
+        // c^{n+1}(p - 1) (from plane p, or bounced: the node's own e_z = +1
+        // values of plane p - 1), each in population order
+        const int pb = (p & 1) ^ 1;
         if (inner && active) {
           if (!closing) {
             double a = 0.0;
@@ -468,13 +456,13 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
               else if ((bmh >> k) & 1u)
                 v = double(hs[LH::opp[k]]);
               else
-                v = double(hx[k][ty - LH::ey[k]][tx - LH::ex[k]]);
+                v = double(hx[xslot(k)][ty - LH::ey[k]][tx - LH::ex[k]]);
               a = a + v;
             }
 #pragma unroll
             for (int k = NU + NM; k < QH; ++k) {
               const double v = ((bmh >> k) & 1u) ? double(hxu[pb][LH::opp[k]][ty][tx])
-                                                 : double(hx[k][ty - LH::ey[k]][tx - LH::ex[k]]);
+                                                 : double(hx[xslot(k)][ty - LH::ey[k]][tx - LH::ex[k]]);
               acc_dn = acc_dn + v;
             }
             acc_up = a;
@@ -486,44 +474,12 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
           }
         }
       }
-      // push form: in-block streaming of h* into the accumulator ring, NPASS
-      // passes: pass j carries population j (e_z=+1, to plane p+1),
-      // population NU+j (e_z=0, to plane p) and population NU+NM+j (e_z=-1,
-      // to plane p-1)
-#pragma unroll
-      for (int j = 0; j < (kGather ? 0 : NPASS); ++j) {
-        if (j < NU && up_ok) {
-          const int k = j;
-          const int tx2 = tx + LH::ex[k], ty2 = ty + LH::ey[k];
-          if (valid && tx2 >= 1 && tx2 <= TX && ty2 >= 1 && ty2 <= TY) {
-            double& a = acc[ring3(p + 1)][ty2][tx2];
-            a = k == 0 ? double(hs[k]) : a + double(hs[k]);
-          }
-        }
-        if (j < NM && own_p) {
-          const int k = NU + j;
-          const int tx2 = tx + LH::ex[k], ty2 = ty + LH::ey[k];
-          if (valid && tx2 >= 1 && tx2 <= TX && ty2 >= 1 && ty2 <= TY) {
-            double& a = acc[sA][ty2][tx2];
-            a = a + double(hs[k]);
-          }
-        }
-        if (j < ND && dn_ok) {
-          const int k = NU + NM + j;
-          const int tx2 = tx + LH::ex[k], ty2 = ty + LH::ey[k];
-          if (valid && tx2 >= 1 && tx2 <= TX && ty2 >= 1 && ty2 <= TY) {
-            double& a = acc[ring3(p - 1)][ty2][tx2];
-            a = a + double(hs[k]);
-          }
-        }
-        __syncthreads();
-      }
 
       // g collision of step n+1 at plane p-1
       if (out && dn_ok) {
         const int zq = wrap_coord(p - 1, nz);
         const int sB = ring3(p - 1);
-        const double c1 = kGather ? acc_dn : acc[kGather ? 0 : sB][ty][tx];
+        const double c1 = acc_dn;
         const C phi1 = phiB[sB][ty][tx];
         const C mu1 = C(closure(K.q, c1, double(phi1)));
         const int zm = (wz && p - 1 == 0) ? 0 : -1, zpl = (wz && p - 1 == nz - 1) ? 0 : 1;
@@ -542,48 +498,46 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
         C G[Q];
         phi_sources<L, C>(K, phi1, mu1, n1, G);
         const auto Gw = make_rsrc(reinterpret_cast<char*>(b.Gn) + zq * groupB, uint32_t(groupB));
-        if constexpr (sizeof(S) < sizeof(double)) {
-          // storage narrower than double: the zeroth moment of the stored g
-          // is balanced through the rest population (balance_g_rest), each
-          // moving population stored as soon as it is computed
-          // sg_old: the double sum of these g, taken when they were pulled
-          double s = 0.0;
+        // storage narrower than double: the zeroth moment of the stored g is
+        // balanced through the rest population (balance_g_rest), each moving
+        // population stored as soon as it is computed; sg_old is the double
+        // sum of these g, taken when they were pulled
+        double s = 0.0;
 #pragma unroll
-          for (int k = 0; k < Q; ++k) {
-            C gk;
-            if constexpr (kRegs)
-              gk = g_old[k];
-            else
-              gk = gkeep[(p - 1) & 1][k][ty - 1][tx - 1];
-            if (k == L::REST) continue;
-            const S v = S(g_collide<L, C>(K, k, gk, phi1, G[k]));
-            bstore_nt<S>(v, Gw, selfB, k * planeB);
-            s = s + double(v);
-          }
+        for (int k = 0; k < Q; ++k) {
+          if (sizeof(S) < sizeof(double) && k == L::REST) continue;
+          C gk;
+          if constexpr (kRegs)
+            gk = g_old[k];
+          else
+            gk = gkeep[k][ty - 1][tx - 1];
+          const S v = S(g_collide<L, C>(K, k, gk, phi1, G[k]));
+          bstore_nt<S>(v, Gw, selfB, k * planeB);
+          if (sizeof(S) < sizeof(double)) s = s + double(v);
+        }
+        if constexpr (sizeof(S) < sizeof(double)) {
           const double wg = K.omega_g_d;
           const double m0 = ((1.0 - wg) * sg_old + wg * double(phi1)) +
                             (1.0 - 0.5 * wg) * double(source_moment<C>(K, phi1, mu1));
           bstore_nt<S>(S(m0 - s), Gw, selfB, L::REST * planeB);
-        } else {
-#pragma unroll
-          for (int k = 0; k < Q; ++k) {
-            C gk;
-            if constexpr (kRegs)
-              gk = g_old[k];
-            else
-              gk = gkeep[(p - 1) & 1][k][ty - 1][tx - 1];
-            bstore_nt<S>(S(g_collide<L, C>(K, k, gk, phi1, G[k])), Gw, selfB, k * planeB);
-          }
         }
       }
       if constexpr (kRegs) {
 #pragma unroll
-        for (int k = 0; k < Q; ++k) g_old[k] = g_new[k];
+        for (int k = 0; k < Q; ++k) g_old[k] = C(gv[k]);
+      } else {
+        if (inner) {
+#pragma unroll
+          for (int k = 0; k < Q; ++k) gkeep[k][ty - 1][tx - 1] = C(gv[k]);
+        }
+      }
+      if constexpr (kPrefetchG) {
+        if (p < z1) fetch_g(p + 1, gv);
       }
       sg_old = sg;
       if constexpr (kWalls) {
         acc_dn = acc_up;
-      } else if constexpr (kGather) {
+      } else {
         acc_dn = acc_mid;
         acc_mid = acc_up;
       }
@@ -598,27 +552,35 @@ inline bool fused3d_supported(int nx, int ny, int nz, const int*) {
   return (int64_t)nx * ny * 19 * 8 < ((int64_t)1 << 32) && (int64_t)nx * ny * nz < ((int64_t)1 << 31);
 }
 
-// Domains with a zero-flux wall take the gather form of the in-block
-// streaming, so FP64 on D3Q19 carries g in registers there, on 64 x 5 tiles
-// (one 8-wave block per CU; 512^3: 20.25 ms against 20.08 ms periodic).
-template <class L, class S>
-struct Fused3DWallConfig : Fused3DConfig<L, S> {};
-template <>
-struct Fused3DWallConfig<D3Q19, double> {
+// With zero-flux walls the e_z = +1 layer of the exchange is kept twice, so
+// D3Q19 carries g in registers: FP64 on 64 x 5 tiles (one 8-wave block per
+// CU; 512^3 20.5 ms against 20.6 without the prefetch, 256^3 2.45 against
+// 2.61; carry in the LDS 21.0, 2.56), FP32 on 64 x 9 (12 waves; 9.95 against
+// 11.0 ms, 1.29 against 1.38; 8 rows 10.4; carry in the LDS 10.4), in
+// 32-plane chunks.
+template <class L, class LH, class S>
+struct Fused3DWallConfig : Fused3DConfig<L, LH, S> {};
+template <class LH>
+struct Fused3DWallConfig<D3Q19, LH, double> {
   static constexpr int TX = 64, TY = 5, ZC = 32;
   static constexpr Carry carry = Carry::kRegisters;
-  static constexpr bool prefetch = false;
+  static constexpr Prefetch prefetch = Prefetch::kBoth;
 };
-// FP32 on D3Q19 with walls: 64 x 9 tiles (12 waves, 142 VGPRs, no spill),
-// 11.01 ms per 512^3 step against 11.33 on the 64 x 12 tiles of the
-// periodic grid (which spill about 25 VGPRs with walls; the order was the
-// reverse before the tile columns turned per chunk, 12.43 against 11.95),
-// 32-plane chunks, and without the prefetch of the periodic grid (which
-// spills 45 VGPRs there: 19.0 against 16.3 ms)
-template <>
-struct Fused3DWallConfig<D3Q19, float> : Fused3DConfig<D3Q19, float> {
-  static constexpr int TY = 9, ZC = 32;
-  static constexpr bool prefetch = false;
+template <class LH>
+struct Fused3DWallConfig<D3Q19, LH, float> {
+  static constexpr int TX = 64, TY = 9, ZC = 32;
+  static constexpr Carry carry = Carry::kRegisters;
+  static constexpr Prefetch prefetch = Prefetch::kBoth;
+};
+
+// The general instantiation in FP64 with h on D3Q19 needs the registers of 8
+// waves (64 x 5 tiles, g carried in registers: 512^3 20.6 and 21.0 ms with
+// general free energies and with h^eq,alt, against 21.3 in the form before and
+// 21.8 on the basic form's tiles), and with walls those of the prefetch.
+struct Fused3DGeneralConfig {
+  static constexpr int TX = 64, TY = 5, ZC = 32;
+  static constexpr Carry carry = Carry::kRegisters;
+  static constexpr Prefetch prefetch = Prefetch::kNone;
 };
 
 template <class L, class LH, class S, class C, bool kGen>
@@ -641,8 +603,11 @@ struct Fused3D {
     return 0;
   }
   static int launch(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {
-    if (g.bcx || g.bcy || g.bcz) return run<Fused3DWallConfig<L, S>, true>(g, K, b, st);
-    return run<Fused3DConfig<L, S>, false>(g, K, b, st);
+    constexpr bool kGeneral = kGen && sizeof(S) == 8 && LH::Q == 19;
+    using Walls = std::conditional_t<kGeneral, Fused3DGeneralConfig, Fused3DWallConfig<L, LH, S>>;
+    using Periodic = std::conditional_t<kGeneral, Fused3DGeneralConfig, Fused3DConfig<L, LH, S>>;
+    if (g.bcx || g.bcy || g.bcz) return run<Walls, true>(g, K, b, st);
+    return run<Periodic, false>(g, K, b, st);
   }
 };
 
