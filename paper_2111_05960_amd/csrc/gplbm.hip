@@ -263,10 +263,6 @@ void by_addr(const gplbm_ctx* ctx, const F& f) {
 // arithmetic types S, C.
 template <class L, class LH, class S, class C>
 struct Ops {
-  static dim3 block() { return dim3(64, 4, 1); }
-  static dim3 grid(const gplbm_ctx* ctx) {
-    return dim3((ctx->p.nx + 63) / 64, (ctx->p.ny + 3) / 4, ctx->p.nz);
-  }
   static Coef<C> coef(const gplbm_ctx* ctx) { return make_coef<C>(ctx->p); }
   // the alternative h scheme or the general free energies
   static bool general(const gplbm_ctx* ctx) {
@@ -276,8 +272,10 @@ struct Ops {
   static int init(gplbm_ctx* ctx, const double* phi0, const double* c0) {
     const Geo g = make_geo(ctx->p);
     const int a = ctx->cur;
-    hipLaunchKernelGGL((k_init<L, LH, S, C>), grid(ctx), block(), 0, ctx->stream, g, coef(ctx), phi0,
-                       c0, (S*)ctx->G[a], (S*)ctx->H[a], (S*)ctx->PHI[a]);
+    by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+      hipLaunchKernelGGL((k_init<L, LH, S, C, typename decltype(addr)::type>), gr, bl, 0, ctx->stream,
+                         g, coef(ctx), phi0, c0, (S*)ctx->G[a], (S*)ctx->H[a], (S*)ctx->PHI[a]);
+    });
     return check_launch(ctx, "init");
   }
 
@@ -327,8 +325,10 @@ struct Ops {
   static int fields(gplbm_ctx* ctx, double* phi, double* c, double* mu) {
     const Geo g = make_geo(ctx->p);
     const int a = ctx->cur;
-    hipLaunchKernelGGL((k_fields<LH, S>), grid(ctx), block(), 0, ctx->stream, g,
-                       closure_k(ctx->p), (const S*)ctx->H[a], (const S*)ctx->PHI[a], phi, c, mu);
+    by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+      hipLaunchKernelGGL((k_fields<LH, S, typename decltype(addr)::type>), gr, bl, 0, ctx->stream, g,
+                         closure_k(ctx->p), (const S*)ctx->H[a], (const S*)ctx->PHI[a], phi, c, mu);
+    });
     return check_launch(ctx, "read fields");
   }
 
@@ -337,8 +337,11 @@ struct Ops {
     const int a = ctx->cur;
     double* part = red;
     double* out = red + kDiagBlocks * kDiagVals;
-    hipLaunchKernelGGL((k_diag_partial<LH, S>), dim3(kDiagBlocks), dim3(kDiagThreads), 0,
-                       ctx->stream, g, (const S*)ctx->H[a], (const S*)ctx->PHI[a], part);
+    by_addr(ctx, [&](auto addr, dim3, dim3) {
+      hipLaunchKernelGGL((k_diag_partial<LH, S, typename decltype(addr)::type>), dim3(kDiagBlocks),
+                         dim3(kDiagThreads), 0, ctx->stream, g, (const S*)ctx->H[a],
+                         (const S*)ctx->PHI[a], part);
+    });
     hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kDiagThreads), 0, ctx->stream,
                        (const double*)part, kDiagBlocks, out);
     return check_launch(ctx, "diagnostics");
@@ -368,7 +371,10 @@ struct DevOps {
     const Coef<float> K = make_coef<float>(ctx->p);
     const DevState s = state(ctx, ctx->cur);
     hipLaunchKernelGGL(k_dev_init_fields, grid(ctx), block(), 0, ctx->stream, g, K, phi0, c0, s);
-    hipLaunchKernelGGL((k_dev_init<Codec, L, LH>), grid(ctx), block(), 0, ctx->stream, g, K, c0, s);
+    by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+      hipLaunchKernelGGL((k_dev_init<Codec, L, LH, typename decltype(addr)::type>), gr, bl, 0,
+                         ctx->stream, g, K, c0, s);
+    });
     return check_launch(ctx, "init");
   }
   static int step(gplbm_ctx* ctx, int64_t nsteps) {
@@ -404,16 +410,21 @@ struct DevOps {
   }
   static int fields(gplbm_ctx* ctx, double* phi, double* c, double* mu) {
     const Geo g = make_geo(ctx->p);
-    hipLaunchKernelGGL((k_dev_fields<Codec, LH>), grid(ctx), block(), 0, ctx->stream, g,
-                       closure_k(ctx->p), state(ctx, ctx->cur), phi, c, mu);
+    by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+      hipLaunchKernelGGL((k_dev_fields<Codec, LH, typename decltype(addr)::type>), gr, bl, 0,
+                         ctx->stream, g, closure_k(ctx->p), state(ctx, ctx->cur), phi, c, mu);
+    });
     return check_launch(ctx, "read fields");
   }
   static int diag(gplbm_ctx* ctx, double* red) {
     const Geo g = make_geo(ctx->p);
     double* part = red;
     double* out = red + kDiagBlocks * kDiagVals;
-    hipLaunchKernelGGL((k_dev_diag_partial<Codec, LH>), dim3(kDiagBlocks), dim3(kDiagThreads), 0,
-                       ctx->stream, g, state(ctx, ctx->cur), part);
+    by_addr(ctx, [&](auto addr, dim3, dim3) {
+      hipLaunchKernelGGL((k_dev_diag_partial<Codec, LH, typename decltype(addr)::type>),
+                         dim3(kDiagBlocks), dim3(kDiagThreads), 0, ctx->stream, g,
+                         state(ctx, ctx->cur), part);
+    });
     hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kDiagThreads), 0, ctx->stream,
                        (const double*)part, kDiagBlocks, out);
     return check_launch(ctx, "diagnostics");
@@ -886,15 +897,13 @@ struct FwdFromState<DevFwdState<Codec>> {
 
 template <class L, class LH, class FS>
 struct AdjOps {
-  static dim3 block() { return dim3(64, 4, 1); }
-  static dim3 grid(const gplbm_ctx* ctx) {
-    return dim3((ctx->p.nx + 63) / 64, (ctx->p.ny + 3) / 4, ctx->p.nz);
-  }
   static double lam_M_W2(const gplbm_ctx* ctx) { return ctx->p.M_phi / (ctx->p.W * ctx->p.W); }
   static int seed(gplbm_ctx* ctx, const double* phib, const double* cb) {
     const Geo g = make_geo(ctx->p);
-    hipLaunchKernelGGL((k_adj_seed<L, LH>), grid(ctx), block(), 0, ctx->stream, g, phib, cb,
-                       ctx->adj.set[ctx->adj_cur], ctx->adj);
+    by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+      hipLaunchKernelGGL((k_adj_seed<L, LH, typename decltype(addr)::type>), gr, bl, 0, ctx->stream, g,
+                         phib, cb, ctx->adj.set[ctx->adj_cur], ctx->adj);
+    });
     return check_launch(ctx, "adjoint seed");
   }
   static int step(gplbm_ctx* ctx, const void* s0, const void* s1) {
@@ -902,23 +911,19 @@ struct AdjOps {
     const Coef<double> K = make_coef<double>(ctx->p);
     const int a = ctx->adj_cur, b = 1 - a;
     const FS S0 = FwdFromState<FS>::get(ctx, s0), S1 = FwdFromState<FS>::get(ctx, s1);
-    // the general reverse kernels only for h^eq,alt or eps_s != eps_l; the
-    // periodic addressing when no axis has walls
+    // the general reverse kernels only for h^eq,alt or eps_s != eps_l
     const bool gen = ctx->p.h_scheme != GPLBM_H_SOURCE || ctx->p.free_energy != GPLBM_FE_EQUAL;
-    const bool per = !ctx->p.bc[0] && !ctx->p.bc[1] && !ctx->p.bc[2];
-    auto launch = [&](auto kgen, auto kper) {
-      constexpr bool G = decltype(kgen)::value, Pr = decltype(kper)::value;
-      hipLaunchKernelGGL((k_adj_ra<L, LH, FS, G, Pr>), grid(ctx), block(), 0, ctx->stream, g, K,
-                         lam_M_W2(ctx), S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
-      hipLaunchKernelGGL((k_adj_rb<L, LH, FS, G, Pr>), grid(ctx), block(), 0, ctx->stream, g, K,
-                         lam_M_W2(ctx), S0, S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
-    };
-    using T = std::true_type;
-    using F = std::false_type;
-    if (gen)
-      per ? launch(T{}, T{}) : launch(T{}, F{});
-    else
-      per ? launch(F{}, T{}) : launch(F{}, F{});
+    by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+      using A = typename decltype(addr)::type;
+      auto launch = [&](auto kgen) {
+        constexpr bool G = decltype(kgen)::value;
+        hipLaunchKernelGGL((k_adj_ra<L, LH, FS, G, A>), gr, bl, 0, ctx->stream, g, K, lam_M_W2(ctx),
+                           S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
+        hipLaunchKernelGGL((k_adj_rb<L, LH, FS, G, A>), gr, bl, 0, ctx->stream, g, K, lam_M_W2(ctx),
+                           S0, S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
+      };
+      gen ? launch(std::true_type{}) : launch(std::false_type{});
+    });
     int rc = check_launch(ctx, "adjoint step");
     if (rc) return rc;
     ctx->adj_cur = b;
@@ -929,14 +934,16 @@ struct AdjOps {
     const Geo g = make_geo(ctx->p);
     const Coef<double> K = make_coef<double>(ctx->p);
     const int a = ctx->adj_cur, b = 1 - a;
-    hipLaunchKernelGGL((k_adj_init_a<L, LH>), grid(ctx), block(), 0, ctx->stream, g, K, lam_M_W2(ctx),
-                       phi0, c0, ctx->adj.set[a], ctx->adj.set[b], ctx->adj, c0b);
-    hipLaunchKernelGGL((k_adj_init_b<L>), grid(ctx), block(), 0, ctx->stream, g, ctx->adj.set[b],
-                       phi0b);
+    by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
+      using A = typename decltype(addr)::type;
+      hipLaunchKernelGGL((k_adj_init_a<L, LH, A>), gr, bl, 0, ctx->stream, g, K, lam_M_W2(ctx), phi0,
+                         c0, ctx->adj.set[a], ctx->adj.set[b], ctx->adj, c0b);
+      hipLaunchKernelGGL((k_adj_init_b<L, A>), gr, bl, 0, ctx->stream, g, ctx->adj.set[b], phi0b);
+    });
     hipLaunchKernelGGL(k_adj_reduce, dim3(kDiagBlocks), dim3(kDiagThreads), 0, ctx->stream,
                        (const double*)ctx->adj.lamb, (const double*)ctx->adj.dlb, g.N, ctx->adj.red);
-    hipLaunchKernelGGL(k_adj_reduce_final, dim3(1), dim3(64), 0, ctx->stream,
-                       (const double*)ctx->adj.red, kDiagBlocks, ctx->adj.red + 2 * kDiagBlocks);
+    hipLaunchKernelGGL(k_adj_reduce_final, dim3(1), dim3(kDiagThreads), 0, ctx->stream,
+                       (const double*)ctx->adj.red, ctx->adj.red + 2 * kDiagBlocks);
     return check_launch(ctx, "adjoint finish");
   }
 };

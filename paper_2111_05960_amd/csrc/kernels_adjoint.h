@@ -22,7 +22,12 @@
 //       stencil transpose of A2), reverse of the h collision of step n and of
 //       phi^{n+1} = sum g~^{n+1} + S^n / 2: B1, B2, B3, B4.
 // The transposes of the pulls and of the gradient stencil are done as gathers
-// by the consumer, so the adjoint of a state is never written out.
+// by the consumer, so the adjoint of a state is never written out.  Bound by
+// memory on large grids (256^3 D3Q19: 19.2 GB of algorithmic bytes in 4.2 ms
+// with threads over 64 x 4 tiles and 64-bit indices, 3.8 ms with threads over
+// the nodes of a plane, scalar plane bases and every load issued first) and by
+// latency and idle lanes on small ones (96^3 290 -> 217 us, with walls 485 ->
+// 243 us).
 // Parameters are held fixed except lambda and D_l (gamma, M_phi, W and a do
 // not follow D_l).
 #pragma once
@@ -74,120 +79,12 @@ struct DevFwdState {
   const float* LAM;
 };
 
-// Destination of the value stored in slot (k, x, y, z) under the pull
-// streaming: the node x + e_k reads it as population k, or, when x + e_k
-// lies beyond a zero-flux wall, x itself reads it as population opp(k).
-// Returns the destination population; (dx, dy, dz) the destination node.
-template <class L>
-__device__ __forceinline__ int push_dest(const Geo& g, int k, int x, int y, int z, int& dx, int& dy,
-                                         int& dz) {
-  dx = x;
-  dy = y;
-  dz = z;
-  // moving "backwards" by -e_k with pull_axis gives x + e_k
-  bool in = pull_axis(dx, -L::ex[k], g.nx, g.bcx) && pull_axis(dy, -L::ey[k], g.ny, g.bcy);
-  if (L::D == 3) in = in && pull_axis(dz, -L::ez[k], g.nz, g.bcz);
-  if (!in) {
-    dx = x;
-    dy = y;
-    dz = z;
-    return L::opp[k];
-  }
-  return k;
-}
-
-// Addressing of the reverse steps.  AdjAddrGeneral takes any boundary, by
-// the rules of geometry.h; AdjAddrPeriodic serves grids periodic on every
-// axis, where each neighbour is the node plus a wrapped offset (precomputed
-// per node, the plane ones uniform over a block), without the per-population
-// wall tests.  Both give the same indices on a periodic grid.
-struct AdjAddrGeneral {
-  const Geo& g;
-  int x, y, z;
-  __device__ AdjAddrGeneral(const Geo& g_, int x_, int y_, int z_) : g(g_), x(x_), y(y_), z(z_) {}
-  __device__ int64_t self() const { return node_index(g, x, y, z); }
-  // slot that population k of lattice P pulls at this node: (k, x - e_k), or
-  // (opp k, x) when x - e_k lies beyond a wall
-  template <class P>
-  __device__ int64_t pull_slot(int k) const {
-    int sx = x, sy = y, sz = z;
-    bool in = pull_axis(sx, P::ex[k], g.nx, g.bcx) && pull_axis(sy, P::ey[k], g.ny, g.bcy);
-    if (P::D == 3) in = in && pull_axis(sz, P::ez[k], g.nz, g.bcz);
-    if (!in) return pop_index<P>(g, P::opp[k], x, y, z);
-    return pop_index<P>(g, k, sx, sy, sz);
-  }
-  // node and population that pull slot k of this node
-  template <class P>
-  __device__ void push(int k, int64_t& dpop, int64_t& dnode) const {
-    int dx, dy, dz;
-    const int kk = push_dest<P>(g, k, x, y, z, dx, dy, dz);
-    dpop = pop_index<P>(g, kk, dx, dy, dz);
-    dnode = node_index(g, dx, dy, dz);
-  }
-  // source node of the value population k of lattice P pulls (the node
-  // itself for a bounced population), and its slot in the deviation layout
-  template <class P>
-  __device__ void pull_dev_slot(int k, int64_t& node, int64_t& slot, int& kk) const {
-    int sx = x, sy = y, sz = z;
-    bool in = pull_axis(sx, P::ex[k], g.nx, g.bcx) && pull_axis(sy, P::ey[k], g.ny, g.bcy);
-    if (P::D == 3) in = in && pull_axis(sz, P::ez[k], g.nz, g.bcz);
-    kk = in ? k : P::opp[k];
-    if (!in) sx = x, sy = y, sz = z;
-    node = node_index(g, sx, sy, sz);
-    slot = mov_index<P>(g, kk, sx, sy, sz);
-  }
-  // node x + (dx, dy, dz) of the gradient stencil (mirror ghost at walls)
-  __device__ int64_t stencil(int dx, int dy, int dz) const {
-    return node_index(g, stencil_axis(x + dx, g.nx, g.bcx), stencil_axis(y + dy, g.ny, g.bcy),
-                      stencil_axis(z + dz, g.nz, g.bcz));
-  }
+// Population planes of a distribution, and of a field.
+struct PopPlane {
+  __device__ int operator()(int k) const { return k; }
 };
-
-struct AdjAddrPeriodic {
-  int64_t plane;
-  int z, zm, zp;             // planes z, z - 1, z + 1 (wrapped)
-  int xy;                    // y nx + x
-  int oxm, oxp, oym, oyp;    // in-plane offsets of x - 1, x + 1, y - 1, y + 1 (wrapped)
-  __device__ AdjAddrPeriodic(const Geo& g, int x, int y, int z_) {
-    plane = (int64_t)g.nx * g.ny;
-    z = z_;
-    zm = z == 0 ? g.nz - 1 : z - 1;
-    zp = z == g.nz - 1 ? 0 : z + 1;
-    xy = y * g.nx + x;
-    oxm = x == 0 ? g.nx - 1 : -1;
-    oxp = x == g.nx - 1 ? 1 - g.nx : 1;
-    oym = y == 0 ? (g.ny - 1) * g.nx : -g.nx;
-    oyp = y == g.ny - 1 ? (1 - g.ny) * g.nx : g.nx;
-  }
-  __device__ int xyn(int dx, int dy) const {
-    return xy + (dx < 0 ? oxm : (dx > 0 ? oxp : 0)) + (dy < 0 ? oym : (dy > 0 ? oyp : 0));
-  }
-  __device__ int zn(int dz) const { return dz < 0 ? zm : (dz > 0 ? zp : z); }
-  __device__ int64_t node(int dx, int dy, int dz) const { return (int64_t)zn(dz) * plane + xyn(dx, dy); }
-  __device__ int64_t self() const { return (int64_t)z * plane + xy; }
-  template <class P>
-  __device__ int64_t pull_slot(int k) const {
-    return ((int64_t)zn(-P::ez[k]) * P::Q + k) * plane + xyn(-P::ex[k], -P::ey[k]);
-  }
-  template <class P>
-  __device__ void push(int k, int64_t& dpop, int64_t& dnode) const {
-    dpop = ((int64_t)zn(P::ez[k]) * P::Q + k) * plane + xyn(P::ex[k], P::ey[k]);
-    dnode = node(P::ex[k], P::ey[k], P::ez[k]);
-  }
-  template <class P>
-  __device__ void pull_dev_slot(int k, int64_t& src, int64_t& slot, int& kk) const {
-    kk = k;
-    src = node(-P::ex[k], -P::ey[k], -P::ez[k]);
-    slot = ((int64_t)zn(-P::ez[k]) * (P::Q - 1) + mslot<P>(k)) * plane + xyn(-P::ex[k], -P::ey[k]);
-  }
-  __device__ int64_t stencil(int dx, int dy, int dz) const { return node(dx, dy, dz); }
-};
-
-template <class S, class A>
-struct AddrPhi {
-  const S* __restrict__ f;
-  const A& a;
-  __device__ double operator()(int dx, int dy, int dz) const { return double(f[a.stencil(dx, dy, dz)]); }
+struct FieldPlane {
+  __device__ int operator()(int) const { return 0; }
 };
 
 // Forward quantities at one node from a state: c, mu, phi, grad phi, normal.
@@ -196,93 +93,59 @@ struct NodeFwd {
   double c, mu, phi, g[3], n[3], s;  // s = sqrt(|grad|^2 + eps^2)
 };
 
-template <class L, class LH, class S, class A>
-__device__ __forceinline__ NodeFwd<L> node_fwd_at(const Coef<double>& K, const FwdState<S>& F,
-                                                  const A& a) {
+// c, phi and the stencil values to the forward quantities.
+template <class L>
+__device__ __forceinline__ NodeFwd<L> node_fwd_from(const Coef<double>& K, double c, double phi,
+                                                    const Stencil<L, double>& st) {
   NodeFwd<L> f;
-  double c = 0.0;
-#pragma unroll
-  for (int k = 0; k < LH::Q; ++k) {
-    const double v = double(F.H[a.template pull_slot<LH>(k)]);
-    c = k == 0 ? v : c + v;
-  }
   f.c = c;
-  f.phi = double(F.PHI[a.self()]);
-  f.mu = closure(K.q, c, f.phi);
-  gradient_normal<L, double>(AddrPhi<S, A>{F.PHI, a}, K.eps2, f.g, f.n);
+  f.phi = phi;
+  f.mu = closure(K.q, c, phi);
+  gradient_normal<L, double>(st, K.eps2, f.g, f.n);
   double nn = f.g[0] * f.g[0] + f.g[1] * f.g[1];
   if (L::D == 3) nn = nn + f.g[2] * f.g[2];
   f.s = sqrt(nn + K.eps2);
   return f;
 }
 
-template <class L, class LH, class Codec, class A>
-__device__ __forceinline__ NodeFwd<L> node_fwd_at(const Coef<double>& K, const DevFwdState<Codec>& F,
-                                                  const A& a) {
-  NodeFwd<L> f;
-  double c = 0.0;
-#pragma unroll
-  for (int k = 0; k < LH::Q; ++k) {
-    float v;
-    if (k == LH::REST) {
-      v = F.H.rest[a.self()];
-    } else {
-      int64_t src, slot;
-      int kk;
-      a.template pull_dev_slot<LH>(k, src, slot, kk);
-      v = dev_decode<Codec>(F.H.mov[slot], float(LH::w[kk]) * F.LAM[src]);
-    }
-    c = k == 0 ? double(v) : c + double(v);
-  }
-  f.c = c;
-  f.phi = double(F.PHI[a.self()]);
-  f.mu = closure(K.q, c, f.phi);
-  gradient_normal<L, double>(AddrPhi<float, A>{F.PHI, a}, K.eps2, f.g, f.n);
-  double nn = f.g[0] * f.g[0] + f.g[1] * f.g[1];
-  if (L::D == 3) nn = nn + f.g[2] * f.g[2];
-  f.s = sqrt(nn + K.eps2);
-  return f;
-}
-
+// Loads of a node's forward quantities from a state, and their evaluation.
+template <class L, class LH, class FS>
+struct FwdLoads;
 template <class L, class LH, class S>
-__device__ __forceinline__ NodeFwd<L> node_fwd(const Geo& g, const Coef<double>& K, const FwdState<S>& F,
-                                               int x, int y, int z) {
-  NodeFwd<L> f;
-  double c = 0.0;
+struct FwdLoads<L, LH, FwdState<S>> {
+  Stencil<L, double> st;
+  S hv[LH::Q];
+  template <class A>
+  __device__ FwdLoads(const FwdState<S>& F, const A& a) : st(a, F.PHI) {
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) {
-    const double v = double(pull<LH>(g, F.H, k, x, y, z));
-    c = k == 0 ? v : c + v;
+    for (int k = 0; k < LH::Q; ++k) hv[k] = a.template pull_pop<LH>(F.H, k);
   }
-  f.c = c;
-  f.phi = double(F.PHI[node_index(g, x, y, z)]);
-  f.mu = closure(K.q, c, f.phi);
-  gradient_normal<L, double>(GlobalPhi<S, double>{g, F.PHI, x, y, z}, K.eps2, f.g, f.n);
-  double nn = f.g[0] * f.g[0] + f.g[1] * f.g[1];
-  if (L::D == 3) nn = nn + f.g[2] * f.g[2];
-  f.s = sqrt(nn + K.eps2);
-  return f;
-}
-
+  template <class A>
+  __device__ NodeFwd<L> eval(const Coef<double>& K, const A&) const {
+    double c = 0.0;
+#pragma unroll
+    for (int k = 0; k < LH::Q; ++k) c = k == 0 ? double(hv[k]) : c + double(hv[k]);
+    return node_fwd_from<L>(K, c, st(0, 0, 0), st);
+  }
+};
 template <class L, class LH, class Codec>
-__device__ __forceinline__ NodeFwd<L> node_fwd(const Geo& g, const Coef<double>& K,
-                                               const DevFwdState<Codec>& F, int x, int y, int z) {
-  NodeFwd<L> f;
-  double c = 0.0;
+struct FwdLoads<L, LH, DevFwdState<Codec>> {
+  Stencil<L, double> st;
+  Stencil<LH, float> sl;
+  DevPulls<LH> ph;
+  template <class A>
+  __device__ FwdLoads(const DevFwdState<Codec>& F, const A& a) : st(a, F.PHI), sl(a, F.LAM), ph(a, F.H) {}
+  template <class A>
+  __device__ NodeFwd<L> eval(const Coef<double>& K, const A& a) const {
+    double c = 0.0;
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) {
-    const double v = double(pull_dev<Codec, LH>(g, F.H, F.LAM, k, x, y, z));
-    c = k == 0 ? v : c + v;
+    for (int k = 0; k < LH::Q; ++k) {
+      const double v = double(ph.template value<Codec>(a, sl, k));
+      c = k == 0 ? v : c + v;
+    }
+    return node_fwd_from<L>(K, c, st(0, 0, 0), st);
   }
-  f.c = c;
-  f.phi = double(F.PHI[node_index(g, x, y, z)]);
-  f.mu = closure(K.q, c, f.phi);
-  gradient_normal<L, double>(GlobalPhi<float, double>{g, F.PHI, x, y, z}, K.eps2, f.g, f.n);
-  double nn = f.g[0] * f.g[0] + f.g[1] * f.g[1];
-  if (L::D == 3) nn = nn + f.g[2] * f.g[2];
-  f.s = sqrt(nn + K.eps2);
-  return f;
-}
+};
 
 // Derivatives of the closure mu(c, phi): 1 and c_s - c_l for equal
 // curvatures; for general quadratic free energies, with
@@ -422,32 +285,32 @@ __device__ __forceinline__ double stencil_adj_gather(const Geo& g, const double*
 
 // --------------------------------------------------------------------------
 
-// The same gather on a periodic grid: one preimage per population, x - e_k.
-template <class L>
-__device__ __forceinline__ double stencil_adj_gather_at(const Geo& g, const double* gb3,
-                                                        const AdjAddrPeriodic& a) {
+// The same gather in the addressing of a node: away from walls there is one
+// preimage per population, x - e_k; a wavefront with a node next to a wall
+// takes the general form.
+template <class L, class A>
+__device__ __forceinline__ double stencil_adj_gather_at(const Geo& g, const double* gb3, const A& a) {
+  if (__builtin_amdgcn_ballot_w64(a.edge()) != 0u)
+    return stencil_adj_gather<L>(g, gb3, a.x, a.y, a.z);
   double acc = 0.0;
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) {
     if (k == L::REST) continue;
-    const int64_t q = a.node(-L::ex[k], -L::ey[k], -L::ez[k]);
-    const double e_g = edot<L, double>(k, gb3[q], gb3[g.N + q], L::D == 3 ? gb3[2 * g.N + q] : 0.0);
-    acc += L::inv_cs2 * L::w[k] * e_g;
+    double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int d = 0; d < L::D; ++d)
+      if ((d == 0 && L::ex[k]) || (d == 1 && L::ey[k]) || (d == 2 && L::ez[k]))
+        v[d] = a.at(gb3 + d * g.N, -L::ex[k], -L::ey[k], -L::ez[k]);
+    acc += L::inv_cs2 * L::w[k] * edot<L, double>(k, v[0], v[1], v[2]);
   }
   return acc;
 }
-template <class L>
-__device__ __forceinline__ double stencil_adj_gather_at(const Geo& g, const double* gb3,
-                                                        const AdjAddrGeneral& a) {
-  return stencil_adj_gather<L>(g, gb3, a.x, a.y, a.z);
-}
 
-// Adjoint of G' in slot (k, x, y, z), gathered from the previous set.
-template <class L>
-__device__ __forceinline__ double gather_Gb(const Geo& g, const AdjSet& P, int k, int x, int y, int z) {
-  int dx, dy, dz;
-  const int kk = push_dest<L>(g, k, x, y, z, dx, dy, dz);
-  return P.A1[pop_index<L>(g, kk, dx, dy, dz)] + P.B2[node_index(g, dx, dy, dz)];
+// Adjoint of G' in slot k of the node, gathered from the previous set.
+template <class L, class A>
+__device__ __forceinline__ double gather_Gb(const AdjSet& P, int k, const A& a) {
+  return *a.template dest<L>((const double*)P.A1, k, L::Q, PopPlane{}) +
+         *a.template dest<L>((const double*)P.B2, k, 1, FieldPlane{});
 }
 
 // kGen: the general instantiation keeps the scheme flags (h^eq,alt, general
@@ -455,8 +318,7 @@ __device__ __forceinline__ double gather_Gb(const Geo& g, const AdjSet& P, int k
 // The two halves of a reverse step at one node (the two kernels below).
 //
 // reverse_g: the reverse of the g collision of step n+1.  Writes the adjoint
-// of the node's pulled g~^{n+1} (C.A1) when write_a1 is set, and returns the
-// adjoint of grad phi^{n+1} with the previous step's B3 added (a2), of c^{n+1}
+// of the node's pulled g~^{n+1} (C.A1), and returns the adjoint of grad phi^{n+1} with the previous step's B3 added (a2), of c^{n+1}
 // (a3), the local adjoint of phi^{n+1} with the previous step's B4 added (a4),
 // and the lambda adjoint (lb).  The h collision of step n+1 (previous reverse
 // step) also used grad phi^{n+1} and phi^{n+1}: their adjoints are added here,
@@ -464,58 +326,62 @@ __device__ __forceinline__ double gather_Gb(const Geo& g, const AdjSet& P, int k
 template <class L, class LH, class FS, class Addr>
 __device__ __forceinline__ void reverse_g(const Geo& g, const Coef<double>& K, double lam_M_W2,
                                           const FS& S1, const AdjSet& P, const AdjSet& C,
-                                          const Addr& ad, int z, bool write_a1, double (&a2)[3],
-                                          double& a3, double& a4, double& lb) {
-  const int64_t i = ad.self();
-  const NodeFwd<L> f = node_fwd_at<L, LH>(K, S1, ad);  // c^{n+1}, mu^{n+1}, ...
+                                          const Addr& ad, double (&a2)[3], double& a3,
+                                          double& a4, double& lb) {
+  const int64_t i = ad.node();
+  const FwdLoads<L, LH, FS> fwd(S1, ad);
+  double a_in[L::Q];
+#pragma unroll
+  for (int k = 0; k < L::Q; ++k) a_in[k] = gather_Gb<L>(P, k, ad);
+  double b3[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int a = 0; a < L::D; ++a) b3[a] = P.B3[a * g.N + i];
+  const double b4 = P.B4[i];
+  loads_issued();
+  const NodeFwd<L> f = fwd.eval(K, ad);  // c^{n+1}, mu^{n+1}, ...
   const double om = K.omega_g;
   double Gb[L::Q];
   double phi_b = 0.0, mu_b = 0.0, nb[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) {
-    int64_t dpop, dnode;
-    ad.template push<L>(k, dpop, dnode);
-    const double a = P.A1[dpop] + P.B2[dnode];
-    if (write_a1)
-      C.A1[((int64_t)z * L::Q + k) * ((int64_t)g.nx * g.ny) + (i - (int64_t)z * g.nx * g.ny)] =
-          (1.0 - om) * a;
+    const double a = a_in[k];
+    C.A1[ad.slot(k, L::Q)] = (1.0 - om) * a;
     Gb[k] = (1.0 - 0.5 * om) * a;
     phi_b += om * L::w[k] * a;
   }
   lb = sources_adj<L>(K, lam_M_W2, f.phi, f.mu, f.n, Gb, 0.0, phi_b, mu_b, nb);
   double gb[3] = {0.0, 0.0, 0.0};
   normal_adj<L>(f, nb, gb);
-  for (int a = 0; a < 3; ++a) a2[a] = a < L::D ? gb[a] + P.B3[a * g.N + i] : 0.0;
+  for (int a = 0; a < 3; ++a) a2[a] = a < L::D ? gb[a] + b3[a] : 0.0;
   double dmu_dc, dmu_dphi;
   closure_grad(K, f.c, f.phi, dmu_dc, dmu_dphi);
   a3 = dmu_dc * mu_b;   // adjoint of c^{n+1}
   phi_b += dmu_dphi * mu_b;  // closure
-  a4 = phi_b + P.B4[i];
+  a4 = phi_b + b4;
 }
 
 // reverse_h: the reverse of the h collision of step n and of phi^{n+1} =
-// sum g~^{n+1} + S^n / 2.  a3_at(k, dnode): the a3 of the node that pulls
-// slot k of this node (dnode its global index); p1b: the adjoint of
+// sum g~^{n+1} + S^n / 2.  p1b: the adjoint of
 // phi^{n+1} at this node gathered so far (a4 and the transposed stencil of
 // a2).  Writes B1 .. B4 of the node into C and accumulates its parameter
 // adjoints.
-template <class L, class LH, class FS, class Addr, class FA3>
+template <class L, class LH, class FS, class Addr>
 __device__ __forceinline__ void reverse_h(const Geo& g, const Coef<double>& K, double lam_M_W2,
                                           const FS& S0, const FS& S1, const AdjSet& P,
-                                          const AdjSet& C, const AdjWork& w, const Addr& ad, int z,
-                                          const FA3& a3_at, double p1b) {
-  const int64_t i = ad.self();
+                                          const AdjSet& C, const AdjWork& w, const Addr& ad,
+                                          double p1b) {
+  const int64_t i = ad.node();
+  const FwdLoads<L, LH, FS> fwd(S0, ad);
   // total adjoint of h~*^n in this node's slots
   double Hb[LH::Q];
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) {
-    int64_t dpop, dnode;
-    ad.template push<LH>(k, dpop, dnode);
-    Hb[k] = P.B1[dpop] + a3_at(k, dnode);
-  }
+  for (int k = 0; k < LH::Q; ++k)
+    Hb[k] = *ad.template dest<LH>((const double*)P.B1, k, LH::Q, PopPlane{}) +
+            *ad.template dest<LH>((const double*)w.A3, k, 1, FieldPlane{});
+  const double phi1 = double(S1.PHI[i]), lamb = w.lamb[i], dlb = w.dlb[i];
+  loads_issued();
   // forward quantities of step n
-  const NodeFwd<L> f = node_fwd_at<L, LH>(K, S0, ad);
-  const double phi1 = double(S1.PHI[i]);
+  const NodeFwd<L> f = fwd.eval(K, ad);
   const double dtphi = phi1 - f.phi;
   const double oh = K.omega_h;
   const double Dp = K.Dp;
@@ -576,68 +442,55 @@ __device__ __forceinline__ void reverse_h(const Geo& g, const Coef<double>& K, d
     phi_b += dmu_dphi * mu_b;
   }
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k)
-    C.B1[((int64_t)z * LH::Q + k) * ((int64_t)g.nx * g.ny) + (i - (int64_t)z * g.nx * g.ny)] = hb[k] + c_b;
+  for (int k = 0; k < LH::Q; ++k) C.B1[ad.slot(k, LH::Q)] = hb[k] + c_b;
   C.B2[i] = p1b;
   for (int a = 0; a < 3; ++a) C.B3[a * g.N + i] = gb[a];
   C.B4[i] = phi_b;
-  w.lamb[i] += lb;
-  w.dlb[i] += dl_b;
+  w.lamb[i] = lamb + lb;
+  w.dlb[i] = dlb + dl_b;
 }
 
-// kPer: every axis periodic (AdjAddrPeriodic), else any boundary.
-template <class L, class LH, class FS, bool kGen, bool kPer>
+template <class L, class LH, class FS, bool kGen, class Addr>
 __global__ void __launch_bounds__(256) k_adj_ra(Geo g, Coef<double> Kin, double lam_M_W2,
                                                 FS S1, AdjSet P, AdjSet C, AdjWork w) {
   const Coef<double> K = variant<kGen>(Kin);
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  using Addr = std::conditional_t<kPer, AdjAddrPeriodic, AdjAddrGeneral>;
-  const Addr ad(g, x, y, z);
-  const int64_t i = ad.self();
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
   double a2[3], a3, a4, lb;
-  reverse_g<L, LH>(g, K, lam_M_W2, S1, P, C, ad, z, true, a2, a3, a4, lb);
+  reverse_g<L, LH>(g, K, lam_M_W2, S1, P, C, ad, a2, a3, a4, lb);
   for (int a = 0; a < L::D; ++a) w.A2[a * g.N + i] = a2[a];
   w.A3[i] = a3;
   w.A4[i] = a4;
   w.lamb[i] += lb;
 }
 
-template <class L, class LH, class FS, bool kGen, bool kPer>
+template <class L, class LH, class FS, bool kGen, class Addr>
 __global__ void __launch_bounds__(256) k_adj_rb(Geo g, Coef<double> Kin, double lam_M_W2,
                                                 FS S0, FS S1, AdjSet P, AdjSet C, AdjWork w) {
   const Coef<double> K = variant<kGen>(Kin);
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  using Addr = std::conditional_t<kPer, AdjAddrPeriodic, AdjAddrGeneral>;
-  const Addr ad(g, x, y, z);
-  const int64_t i = ad.self();
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
   // adjoint of phi^{n+1} at this node (A2, A4 hold both collisions' parts)
-  const double p1b = w.A4[i] + stencil_adj_gather_at<L>(g, w.A2, ad);
-  auto a3_at = [&](int, int64_t dnode) { return w.A3[dnode]; };
-  reverse_h<L, LH>(g, K, lam_M_W2, S0, S1, P, C, w, ad, z, a3_at, p1b);
+  const double p1b = w.A4[i] + stencil_adj_gather_at<L>(g, (const double*)w.A2, ad);
+  reverse_h<L, LH>(g, K, lam_M_W2, S0, S1, P, C, w, ad, p1b);
 }
 
 // Seed: the adjoint of S_K from dJ/dphi^K and dJ/dc^K (c^K = sum of the
 // pulled H), written as a set the first reverse step gathers from:
 // Gb = 0, Hb(slot) = dJ/dc^K(dest), Pb = dJ/dphi^K.
-template <class L, class LH>
+template <class L, class LH, class Addr>
 __global__ void __launch_bounds__(256) k_adj_seed(Geo g, const double* __restrict__ phib,
                                                   const double* __restrict__ cb, AdjSet P, AdjWork w) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
   const double cv = cb ? cb[i] : 0.0;
 #pragma unroll
-  for (int k = 0; k < L::Q; ++k) P.A1[pop_index<L>(g, k, x, y, z)] = 0.0;
+  for (int k = 0; k < L::Q; ++k) P.A1[ad.slot(k, L::Q)] = 0.0;
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) P.B1[pop_index<LH>(g, k, x, y, z)] = cv;
+  for (int k = 0; k < LH::Q; ++k) P.B1[ad.slot(k, LH::Q)] = cv;
   P.B2[i] = 0.0;
   for (int a = 0; a < 3; ++a) P.B3[a * g.N + i] = 0.0;
   P.B4[i] = phib ? phib[i] : 0.0;
@@ -648,26 +501,18 @@ __global__ void __launch_bounds__(256) k_adj_seed(Geo g, const double* __restric
 // Adjoint of the initialisation (phi0, c0) -> S_0, local part: writes the
 // adjoint of c0 and, in B4 / B3, the local part of the adjoint of phi0 and the
 // adjoint of grad phi0.
-template <class L, class LH>
+template <class L, class LH, class Addr>
 __global__ void __launch_bounds__(256) k_adj_init_a(Geo g, Coef<double> K, double lam_M_W2,
                                                     const double* __restrict__ phi0,
                                                     const double* __restrict__ c0, AdjSet P,
                                                     AdjSet C, AdjWork w, double* __restrict__ c0b) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
-  const double phi = phi0[i], cin = c0[i];
-  NodeFwd<L> f;
-  f.phi = phi;
-  gradient_normal<L, double>(GlobalPhi<double, double>{g, phi0, x, y, z}, K.eps2, f.g, f.n);
-  {
-    double nn = f.g[0] * f.g[0] + f.g[1] * f.g[1];
-    if (L::D == 3) nn = nn + f.g[2] * f.g[2];
-    f.s = sqrt(nn + K.eps2);
-  }
-  const double mu0 = closure(K.q, cin, phi);
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
+  const Stencil<L, double> st(ad, phi0);
+  const double phi = st(0, 0, 0), cin = c0[i];
+  const NodeFwd<L> f = node_fwd_from<L>(K, cin, phi, st);
+  const double mu0 = f.mu;
   // forward h~^0 and c^0
   double F[3];
   h_flux<L, double>(K, mu0, f.g, f.n, 0.0, false, F);
@@ -681,15 +526,15 @@ __global__ void __launch_bounds__(256) k_adj_init_a(Geo g, Coef<double> K, doubl
   const double mu = closure(K.q, c, phi);
   // adjoints of the pulled h~^0 (from H of S_0) and of G of S_0
   double hb[LH::Q], Gb[L::Q], g0b[L::Q];
-  double phi_b = P.B4[i] + stencil_adj_gather<L>(g, P.B3, x, y, z);
+  double phi_b = P.B4[i] + stencil_adj_gather_at<L>(g, (const double*)P.B3, ad);
   double mu_b = 0.0, mu0_b = 0.0, nb[3] = {0.0, 0.0, 0.0};
   double lb = 0.0;
   const double om = K.omega_g;
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) hb[k] = P.B1[pop_index<LH>(g, k, x, y, z)];  // gathered Hb
+  for (int k = 0; k < LH::Q; ++k) hb[k] = P.B1[ad.slot(k, LH::Q)];  // gathered Hb
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) {
-    const double gsb = gather_Gb<L>(g, P, k, x, y, z);
+    const double gsb = gather_Gb<L>(P, k, ad);
     g0b[k] = (1.0 - om) * gsb;
     Gb[k] = (1.0 - 0.5 * om) * gsb;
     phi_b += om * L::w[k] * gsb;
@@ -748,14 +593,12 @@ __global__ void __launch_bounds__(256) k_adj_init_a(Geo g, Coef<double> K, doubl
   w.dlb[i] += dl_b;
 }
 
-template <class L>
+template <class L, class Addr>
 __global__ void __launch_bounds__(256) k_adj_init_b(Geo g, AdjSet C, double* __restrict__ phi0b) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
-  phi0b[i] = C.B4[i] + stencil_adj_gather<L>(g, C.B3, x, y, z);
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
+  phi0b[i] = C.B4[i] + stencil_adj_gather_at<L>(g, (const double*)C.B3, ad);
 }
 
 // Deterministic sum of the two per-node accumulators (fixed launch shape).
@@ -785,15 +628,19 @@ __global__ void __launch_bounds__(kDiagThreads) k_adj_reduce(const double* __res
   }
 }
 
-__global__ void k_adj_reduce_final(const double* __restrict__ part, int nb, double* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double sa = 0.0, sb = 0.0;
-    for (int b = 0; b < nb; ++b) {
-      sa = sa + part[2 * b];
-      sb = sb + part[2 * b + 1];
-    }
-    out[0] = sa;
-    out[1] = sb;
+// Sum of the block partials, in their order: loaded by all threads into the
+// LDS, then added by one (begin and finish of a 512^2 sweep 146 -> 62 us; one
+// thread reading global memory took 84 us, a wait per partial).
+__global__ void __launch_bounds__(kDiagThreads) k_adj_reduce_final(const double* __restrict__ part,
+                                                                   double* __restrict__ out) {
+  __shared__ double p[2 * kDiagBlocks];
+  for (int b = threadIdx.x; b < 2 * kDiagBlocks; b += blockDim.x) p[b] = part[b];
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double s = 0.0;
+#pragma unroll 16
+    for (int b = 0; b < kDiagBlocks; ++b) s = s + p[2 * b + threadIdx.x];
+    out[threadIdx.x] = s;
   }
 }
 

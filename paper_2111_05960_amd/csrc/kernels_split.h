@@ -31,20 +31,6 @@ struct StepBufs {
   S* __restrict__ Gn;         // g~*^{n+1}
 };
 
-// phi at (x, y, z) + d from global memory with the stencil ghost rule.
-template <class S, class C>
-struct GlobalPhi {
-  const Geo& g;
-  const S* __restrict__ f;
-  int x, y, z;
-  __device__ C operator()(int dx, int dy, int dz) const {
-    int xx = stencil_axis(x + dx, g.nx, g.bcx);
-    int yy = stencil_axis(y + dy, g.ny, g.bcy);
-    int zz = stencil_axis(z + dz, g.nz, g.bcz);
-    return C(f[node_index(g, xx, yy, zz)]);
-  }
-};
-
 // Addressing of the per-node kernels.  AddrGeneral takes any grid, by the
 // rules of geometry.h.  AddrPlane serves grids whose population planes are
 // shorter than 4 GiB: threads run over the nodes of a z plane (blockIdx.y), so
@@ -57,6 +43,7 @@ struct AddrGeneral {
   __device__ AddrGeneral(const Geo& g_)
       : g(g_), x(blockIdx.x * blockDim.x + threadIdx.x), y(blockIdx.y * blockDim.y + threadIdx.y),
         z(blockIdx.z) {}
+  __device__ AddrGeneral(const Geo& g_, int x_, int y_, int z_) : g(g_), x(x_), y(y_), z(z_) {}
   __device__ bool inside() const { return x < g.nx && y < g.ny; }
   __device__ int64_t node() const { return node_index(g, x, y, z); }
   // element of plane m among the q planes per z of a distribution
@@ -77,8 +64,20 @@ struct AddrGeneral {
       sx = x, sy = y, sz = z, kk = P::opp[k];
     return f + ((int64_t)sz * q + m(kk)) * ((int64_t)g.nx * g.ny) + (int64_t)sy * g.nx + sx;
   }
+  // address that pulls slot k of this node: population k at x + e_k, or
+  // opp(k) at x when x + e_k lies beyond a wall
+  template <class P, class S, class M>
+  __device__ const S* dest(const S* f, int k, int q, const M& m) const {
+    int dx = x, dy = y, dz = z, kk = k;
+    if (!(pull_axis(dx, -P::ex[k], g.nx, g.bcx) && pull_axis(dy, -P::ey[k], g.ny, g.bcy) &&
+          pull_axis(dz, -P::ez[k], g.nz, g.bcz)))
+      dx = x, dy = y, dz = z, kk = P::opp[k];
+    return f + ((int64_t)dz * q + m(kk)) * ((int64_t)g.nx * g.ny) + (int64_t)dy * g.nx + dx;
+  }
   template <class P, class S>
   __device__ S pull_pop(const S* __restrict__ f, int k) const { return pull<P>(g, f, k, x, y, z); }
+  // a wall lies next to the node
+  __device__ bool edge() const { return true; }
   template <class S>
   __device__ S at(const S* __restrict__ f, int dx, int dy, int dz) const {
     return f[node_index(g, stencil_axis(x + dx, g.nx, g.bcx), stencil_axis(y + dy, g.ny, g.bcy),
@@ -90,6 +89,7 @@ template <bool kWalls>
 struct AddrPlane {
   int64_t plane;
   bool in;
+  int x, y, z;
   int zs[3], ps[3];    // planes z - 1, z, z + 1: wrapped, and with the mirror ghost
   uint32_t src[3][3];  // in-plane offset of (x, y) + (c - 1, a - 1), wrapped, [a][c]
   bool xm, xp, ym, yp, zm, zp;  // that neighbour lies beyond a wall
@@ -97,7 +97,16 @@ struct AddrPlane {
   __device__ AddrPlane(const Geo& g) : plane((int64_t)g.nx * g.ny) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     in = i < (uint32_t)plane;
-    const int y = in ? i / (uint32_t)g.nx : 0, x = in ? i - y * g.nx : 0, z = blockIdx.y;
+    const int yy = in ? i / (uint32_t)g.nx : 0;
+    set(g, in ? i - yy * g.nx : 0, yy, blockIdx.y);
+  }
+  __device__ AddrPlane(const Geo& g, int x_, int y_, int z_) : plane((int64_t)g.nx * g.ny), in(true) {
+    set(g, x_, y_, z_);
+  }
+  __device__ void set(const Geo& g, int x_, int y_, int z_) {
+    x = x_;
+    y = y_;
+    z = z_;
     const int xo[3] = {x == 0 ? g.nx - 1 : x - 1, x, x == g.nx - 1 ? 0 : x + 1};
     const int yo[3] = {y == 0 ? g.ny - 1 : y - 1, y, y == g.ny - 1 ? 0 : y + 1};
 #pragma unroll
@@ -141,10 +150,19 @@ struct AddrPlane {
     if (kWalls && bounced<P>(k)) p = elem(f + ((int64_t)zs[1] * q + m(P::opp[k])) * plane, self());
     return p;
   }
+  template <class P, class S, class M>
+  __device__ const S* dest(const S* f, int k, int q, const M& m) const {
+    const S* p = elem(f + ((int64_t)zs[1 + P::ez[k]] * q + m(k)) * plane,
+                      src[1 + P::ey[k]][1 + P::ex[k]]);
+    if (kWalls && bounced<P>(P::opp[k]))
+      p = elem(f + ((int64_t)zs[1] * q + m(P::opp[k])) * plane, self());
+    return p;
+  }
   template <class P, class S>
   __device__ S pull_pop(const S* __restrict__ f, int k) const {
     return *source<P>(f, k, P::Q, [](int j) { return j; });
   }
+  __device__ bool edge() const { return kWalls && (xm || xp || ym || yp || zm || zp); }
   // field at x + (dx, dy, dz), the mirror ghost at a wall
   template <class S>
   __device__ S at(const S* __restrict__ f, int dx, int dy, int dz) const {
@@ -261,32 +279,25 @@ __global__ void __launch_bounds__(256) k_split_g(Geo g, Coef<C> Kin, StepBufs<S>
 // "unstreamed": each value goes to the slot the pull of the first step reads
 // it from (the inverse of the pull permutation).
 
-template <class L, class LH, class S, class C>
+// Bound by its writes (512^3 FP64 41.9 GB, at 4.6 TB/s): non-temporal, since
+// the state of a large grid outlives no cache (512^3 FP64 9.7 -> 9.0 ms, 320^3
+// FP32 with h on D3Q7 1.22 -> 0.87 ms; regular stores 10.3 and 1.13), and
+// addressed as in the step (64^3 FP32 with walls 19.5 -> 13.2 us).
+template <class L, class LH, class S, class C, class Addr>
 __global__ void __launch_bounds__(256) k_init(Geo g, Coef<C> K, const double* __restrict__ phi0,
                                               const double* __restrict__ c0, S* __restrict__ G,
                                               S* __restrict__ H, S* __restrict__ PHI) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
 
-  const C phi = C(phi0[i]);
-  const double cin = c0[i];
-  C gr[3], n[3];
   // the stencil reads phi0 converted to the arithmetic type
-  struct InitPhi {
-    const Geo& g;
-    const double* __restrict__ f;
-    int x, y, z;
-    __device__ C operator()(int dx, int dy, int dz) const {
-      int xx = stencil_axis(x + dx, g.nx, g.bcx);
-      int yy = stencil_axis(y + dy, g.ny, g.bcy);
-      int zz = stencil_axis(z + dz, g.nz, g.bcz);
-      return C(f[node_index(g, xx, yy, zz)]);
-    }
-  };
-  gradient_normal<L, C>(InitPhi{g, phi0, x, y, z}, K.eps2, gr, n);
+  const Stencil<L, C> st(ad, phi0);
+  const double cin = c0[i];
+  loads_issued();
+  const C phi = st(0, 0, 0);
+  C gr[3], n[3];
+  gradient_normal<L, C>(st, K.eps2, gr, n);
 
   // initial populations from (phi0, c0)
   const C mu0 = C(closure(K.q, cin, double(phi)));
@@ -309,42 +320,34 @@ __global__ void __launch_bounds__(256) k_init(Geo g, Coef<C> K, const double* __
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) {
     C g0 = S(C(L::w[k]) * phi - C(0.5) * G0[k]);
-    G[pop_index<L>(g, k, x, y, z)] = S(g_collide<L, C>(K, k, g0, phi, Gk[k]));
+    __builtin_nontemporal_store(S(g_collide<L, C>(K, k, g0, phi, Gk[k])), &G[ad.slot(k, L::Q)]);
   }
   // h~^0 into the slots the first pull reads
 #pragma unroll
-  for (int k = 0; k < LH::Q; ++k) {
-    int dx = x, dy = y, dz = z;
-    // destination x - e_k of the value arriving at x along k
-    bool in = pull_axis(dx, LH::ex[k], g.nx, g.bcx) && pull_axis(dy, LH::ey[k], g.ny, g.bcy);
-    if (LH::D == 3) in = in && pull_axis(dz, LH::ez[k], g.nz, g.bcz);
-    if (in)
-      H[pop_index<LH>(g, k, dx, dy, dz)] = hs[k];
-    else
-      H[pop_index<LH>(g, LH::opp[k], x, y, z)] = hs[k];
-  }
+  for (int k = 0; k < LH::Q; ++k)
+    __builtin_nontemporal_store(hs[k], const_cast<S*>(ad.template source<LH>(
+                                           (const S*)H, k, LH::Q, [](int j) { return j; })));
   PHI[i] = S(phi);
 }
 
 // ---------------------------------------------------------------------------
 // Read-out of phi^n, c^n, mu^n as doubles.
 
-template <class L, class S>
+template <class L, class S, class Addr>
 __global__ void __launch_bounds__(256) k_fields(Geo g, ClosureK q, const S* __restrict__ H,
                                                 const S* __restrict__ PHI, double* phi_out,
                                                 double* c_out, double* mu_out) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
+  const Addr ad(g);
+  if (!ad.inside()) return;
+  const int64_t i = ad.node();
+  S hv[L::Q];
+#pragma unroll
+  for (int k = 0; k < L::Q; ++k) hv[k] = ad.template pull_pop<L>(H, k);
+  const double phi = double(PHI[i]);
+  loads_issued();
   double c = 0.0;
 #pragma unroll
-  for (int k = 0; k < L::Q; ++k) {
-    double v = double(pull<L>(g, H, k, x, y, z));
-    c = k == 0 ? v : c + v;
-  }
-  const double phi = double(PHI[i]);
+  for (int k = 0; k < L::Q; ++k) c = k == 0 ? double(hv[k]) : c + double(hv[k]);
   if (phi_out) phi_out[i] = phi;
   if (c_out) c_out[i] = c;
   if (mu_out) mu_out[i] = closure(q, c, phi);
@@ -395,30 +398,59 @@ __device__ __forceinline__ void diag_block_reduce(double* v) {
   }
 }
 
-template <class L, class S>
+// Coordinates of the nodes i, i + stride, ... a thread of the reduction
+// visits: the stride as (dx, dy, dz), added with carries, in place of two
+// 64-bit divisions per node (with the pulls in one batch: 256^3 FP64 725 ->
+// 459 us, 512^3 FP16 4.23 -> 1.72 ms).
+struct NodeWalk {
+  int x, y, z, dx, dy, dz;
+  __device__ NodeWalk(const Geo& g, int64_t i, int64_t stride) {
+    x = int(i % g.nx);
+    y = int((i / g.nx) % g.ny);
+    z = int(i / ((int64_t)g.nx * g.ny));
+    dx = int(stride % g.nx);
+    dy = int((stride / g.nx) % g.ny);
+    dz = int(stride / ((int64_t)g.nx * g.ny));
+  }
+  __device__ void next(const Geo& g) {
+    x += dx;
+    y += dy;
+    z += dz;
+    if (x >= g.nx) x -= g.nx, ++y;
+    if (y >= g.ny) y -= g.ny, ++z;
+  }
+};
+
+// One node's c and phi into the partial diagnostics.
+__device__ __forceinline__ void diag_add(double* v, double c, double phi) {
+  v[0] = v[0] + c;
+  v[1] = v[1] + (1.0 - phi);
+  v[2] = v[2] + (phi < 0.5 ? 1.0 : 0.0);
+  v[3] = v[3] + phi;
+  v[4] = fmin(v[4], phi);
+  v[5] = fmax(v[5], phi);
+  if (!isfinite(c) || !isfinite(phi)) v[6] = 1.0;
+}
+
+template <class L, class S, class Addr>
 __global__ void __launch_bounds__(kDiagThreads) k_diag_partial(Geo g, const S* __restrict__ H,
                                                                const S* __restrict__ PHI,
                                                                double* __restrict__ part) {
   double v[kDiagVals] = {0.0, 0.0, 0.0, 0.0, INFINITY, -INFINITY, 0.0, 0.0};
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.N; i += stride) {
-    const int x = int(i % g.nx);
-    const int y = int((i / g.nx) % g.ny);
-    const int z = int(i / ((int64_t)g.nx * g.ny));
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  NodeWalk w(g, i, stride);
+  for (; i < g.N; i += stride, w.next(g)) {
+    const Addr ad(g, w.x, w.y, w.z);
+    S hv[L::Q];
+#pragma unroll
+    for (int k = 0; k < L::Q; ++k) hv[k] = ad.template pull_pop<L>(H, k);
+    const double phi = double(PHI[i]);
+    loads_issued();
     double c = 0.0;
 #pragma unroll
-    for (int k = 0; k < L::Q; ++k) {
-      double hv = double(pull<L>(g, H, k, x, y, z));
-      c = k == 0 ? hv : c + hv;
-    }
-    const double phi = double(PHI[i]);
-    v[0] = v[0] + c;
-    v[1] = v[1] + (1.0 - phi);
-    v[2] = v[2] + (phi < 0.5 ? 1.0 : 0.0);
-    v[3] = v[3] + phi;
-    v[4] = fmin(v[4], phi);
-    v[5] = fmax(v[5], phi);
-    if (!isfinite(c) || !isfinite(phi)) v[6] = 1.0;
+    for (int k = 0; k < L::Q; ++k) c = k == 0 ? double(hv[k]) : c + double(hv[k]);
+    diag_add(v, c, phi);
   }
   diag_block_reduce(v);
   if (threadIdx.x == 0)
