@@ -15,8 +15,9 @@ in a deviation storage format and the FP64 reverse sweep at its decoded
 states.
 
 Checkpointing: forward keeps the state every s = ceil(sqrt(K)) steps;
-backward rebuilds each segment from its checkpoint (gplbm_step_chain, no
-copies) and runs the reverse steps over it (gplbm_adjoint_segment), one call
+backward rebuilds each segment from its checkpoint (gplbm_step_to and
+gplbm_step_chain, no copies) and runs the reverse steps over it
+(gplbm_adjoint_segment and, from the checkpoint, gplbm_adjoint_step), two calls
 each per segment, so memory holds about 2 sqrt(K) states.
 """
 from __future__ import annotations
@@ -67,17 +68,17 @@ class _Run(torch.autograd.Function):
         B.gplbm_adjoint_begin(sim.ctx, _aligned(work), nb, pb.data_ptr() if pb is not None else 0,
                               cb.data_ptr() if cb is not None else 0)
         ck_bytes = B.gplbm_checkpoint_bytes(sim.params)
-        # the s + 1 states of a segment, one after the other at a 256-byte stride
+        # the states n0 + 1 .. n0 + s of a segment, one after the other at a
+        # 256-byte stride; the state n0 is read from its checkpoint
         stride = (ck_bytes + 255) // 256 * 256
-        seg_buf = torch.empty((s + 1) * stride + 256, dtype=torch.uint8, device=dev)
+        seg_buf = torch.empty(s * stride + 256, dtype=torch.uint8, device=dev)
         base = _aligned(seg_buf)
-        off = base - seg_buf.data_ptr()
-        state0 = seg_buf[off:off + ck_bytes]
         for (ck, n0) in reversed(ctx.ckpts):
-            n1 = min(n0 + s, K)
-            state0.copy_(ck)
-            B.gplbm_step_chain(sim.ctx, base, stride, n1 - n0)
-            B.gplbm_adjoint_segment(sim.ctx, base, stride, n1 - n0)
+            m = min(s, K - n0)
+            B.gplbm_step_to(sim.ctx, ck.data_ptr(), base)
+            B.gplbm_step_chain(sim.ctx, base, stride, m - 1)
+            B.gplbm_adjoint_segment(sim.ctx, base, stride, m - 1)
+            B.gplbm_adjoint_step(sim.ctx, ck.data_ptr(), base)
         phi0d, c0d = ctx.inputs
         g_phi0 = torch.empty_like(phi0d)
         g_c0 = torch.empty_like(c0d)

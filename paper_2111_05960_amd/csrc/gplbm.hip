@@ -259,6 +259,16 @@ void by_addr(const gplbm_ctx* ctx, const F& f) {
   }
 }
 
+// f(general instantiation as a true / false type).  The addressing of the very
+// largest planes has only the general one, which reads the run's flags.
+template <class A, class F>
+void by_scheme(bool gen, const F& f) {
+  if constexpr (std::is_same_v<A, AddrGeneral>)
+    f(std::true_type{});
+  else
+    gen ? f(std::true_type{}) : f(std::false_type{});
+}
+
 // Typed operations for the lattices L (g) and LH (h) and the storage /
 // arithmetic types S, C.
 template <class L, class LH, class S, class C>
@@ -288,13 +298,12 @@ struct Ops {
                        (S*)ctx->H[b],       (S*)ctx->PHI[b],       (S*)ctx->G[b]};
       by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
         using A = typename decltype(addr)::type;
-        if (general(ctx)) {
-          hipLaunchKernelGGL((k_split_h<L, LH, S, C, true, A>), gr, bl, 0, ctx->stream, g, K, bufs);
-          hipLaunchKernelGGL((k_split_g<L, LH, S, C, true, A>), gr, bl, 0, ctx->stream, g, K, bufs);
-        } else {
-          hipLaunchKernelGGL((k_split_h<L, LH, S, C, false, A>), gr, bl, 0, ctx->stream, g, K, bufs);
-          hipLaunchKernelGGL((k_split_g<L, LH, S, C, false, A>), gr, bl, 0, ctx->stream, g, K, bufs);
-        }
+        auto launch = [&](auto gen) {
+          constexpr bool G = decltype(gen)::value;
+          hipLaunchKernelGGL((k_split_h<L, LH, S, C, G, A>), gr, bl, 0, ctx->stream, g, K, bufs);
+          hipLaunchKernelGGL((k_split_g<L, LH, S, C, G, A>), gr, bl, 0, ctx->stream, g, K, bufs);
+        };
+        by_scheme<A>(general(ctx), launch);
       });
       int rc = check_launch(ctx, "split step");
       if (rc) return rc;
@@ -619,6 +628,45 @@ int finish_diagnostics(gplbm_ctx* ctx, const double* red, gplbm_diag* out) {
   return GPLBM_OK;
 }
 
+// Copy of the context's current state to (save) or from a saved one: one
+// kernel where the saved state is memory of the context's own device at an
+// address that 16-byte vectors fit, else the runtime's copies, which also reach
+// other devices and host memory.
+int copy_state(gplbm_ctx* ctx, char* saved, bool save) {
+  const int a = ctx->cur;
+  char* const own[4] = {ctx->G[a], ctx->H[a], ctx->PHI[a], ctx->LAM[a]};
+  const size_t bytes[4] = {ctx->pop_bytes, ctx->hpop_bytes, ctx->phi_bytes, ctx->lam_bytes};
+  const char* what = save ? "save" : "load";
+  size_t at = 0;
+  uint64_t total = 0;
+  CopyList c{};
+  for (int j = 0; j < 4; ++j) {
+    c.src[j] = (const StreamVec*)(save ? own[j] : saved + at);
+    c.dst[j] = (StreamVec*)(save ? saved + at : own[j]);
+    c.n[j] = bytes[j] / 16;
+    total += c.n[j];
+    at += bytes[j];
+  }
+  const uint64_t blocks = (total + kStreamThreads - 1) / kStreamThreads;
+  hipPointerAttribute_t attr{};
+  bool local = (uintptr_t)saved % 16 == 0 && blocks <= 0x7fffffffull;
+  if (local && hipPointerGetAttributes(&attr, saved) != hipSuccess) {
+    (void)hipGetLastError();
+    local = false;
+  }
+  if (local && attr.type == hipMemoryTypeDevice && attr.device == ctx->device) {
+    hipLaunchKernelGGL(k_copy_list, dim3((unsigned)blocks), dim3(kStreamThreads), 0, ctx->stream, c);
+    return check_launch(ctx, what);
+  }
+  hipError_t e = hipSuccess;
+  for (int j = 0; j < 4 && e == hipSuccess; ++j)
+    if (bytes[j])
+      e = hipMemcpyAsync(c.dst[j], c.src[j], bytes[j], hipMemcpyDeviceToDevice, ctx->stream);
+  if (e != hipSuccess)
+    return fail(ctx, GPLBM_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
+  return GPLBM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -793,36 +841,13 @@ int gplbm_save_state(gplbm_ctx* ctx, void* dev_dst) {
   if (!ctx || !dev_dst) return GPLBM_E_INVALID;
   if (!ctx->ready) return fail(ctx, GPLBM_E_STATE, "save before init");
   if (int rc = use_device(ctx)) return rc;
-  const int a = ctx->cur;
-  char* d = (char*)dev_dst;
-  const size_t pp = ctx->pop_bytes, hp = ctx->hpop_bytes, ph = ctx->phi_bytes;
-  hipError_t e = hipMemcpyAsync(d, ctx->G[a], pp, hipMemcpyDeviceToDevice, ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d + pp, ctx->H[a], hp, hipMemcpyDeviceToDevice, ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d + pp + hp, ctx->PHI[a], ph, hipMemcpyDeviceToDevice, ctx->stream);
-  if (e == hipSuccess && ctx->lam_bytes)
-    e = hipMemcpyAsync(d + pp + hp + ph, ctx->LAM[a], ctx->lam_bytes, hipMemcpyDeviceToDevice,
-                       ctx->stream);
-  if (e != hipSuccess) return fail(ctx, GPLBM_E_DEVICE, std::string("save: ") + hipGetErrorString(e));
-  return GPLBM_OK;
+  return copy_state(ctx, (char*)dev_dst, true);
 }
 
 int gplbm_load_state(gplbm_ctx* ctx, const void* dev_src, int64_t step) {
   if (!ctx || !dev_src || step < 0) return GPLBM_E_INVALID;
   if (int rc = use_device(ctx)) return rc;
-  const int a = ctx->cur;
-  const char* s = (const char*)dev_src;
-  const size_t pp = ctx->pop_bytes, hp = ctx->hpop_bytes, ph = ctx->phi_bytes;
-  hipError_t e = hipMemcpyAsync(ctx->G[a], s, pp, hipMemcpyDeviceToDevice, ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(ctx->H[a], s + pp, hp, hipMemcpyDeviceToDevice, ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(ctx->PHI[a], s + pp + hp, ph, hipMemcpyDeviceToDevice, ctx->stream);
-  if (e == hipSuccess && ctx->lam_bytes)
-    e = hipMemcpyAsync(ctx->LAM[a], s + pp + hp + ph, ctx->lam_bytes, hipMemcpyDeviceToDevice,
-                       ctx->stream);
-  if (e != hipSuccess) return fail(ctx, GPLBM_E_DEVICE, std::string("load: ") + hipGetErrorString(e));
+  if (int rc = copy_state(ctx, (char*)const_cast<void*>(dev_src), false)) return rc;
   ctx->step = step;
   ctx->ready = true;
   return GPLBM_OK;
@@ -922,7 +947,7 @@ struct AdjOps {
         hipLaunchKernelGGL((k_adj_rb<L, LH, FS, G, A>), gr, bl, 0, ctx->stream, g, K, lam_M_W2(ctx),
                            S0, S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
       };
-      gen ? launch(std::true_type{}) : launch(std::false_type{});
+      by_scheme<A>(gen, launch);
     });
     int rc = check_launch(ctx, "adjoint step");
     if (rc) return rc;

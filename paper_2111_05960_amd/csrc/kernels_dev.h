@@ -920,7 +920,7 @@ struct DevFused3D {
 // population, and two blocks of 8 rows per CU (68 VGPRs) in place of one of 13
 // (114): 512^2 FP16 23.9 -> 10.5 us, 1024^2 55.5 -> 32.1 us, 2048^2 229 -> 147
 // us; 128^2 12.6 -> 4.7 us.
-template <int TX, int TY, class Codec, class L, class LH, bool kGen, bool kWalls>
+template <int TX, int TY, class Codec, class L, class LH, bool kGen, bool kWalls, bool kStream>
 __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     k_dev_fused2d(Geo g, Coef<float> Kin, DevStep b, int tiles_x, int ntiles) {
   const Coef<float> K = variant<kGen>(Kin);
@@ -1035,7 +1035,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
       if (out) {
 #pragma unroll
         for (int k = 0; k < QH; ++k)
-          if (k != LH::REST) b.nxt.H.mov[mh(k) * at.plane + i] = enc[k];
+          if (k != LH::REST) store_state<kStream>(enc[k], &b.nxt.H.mov[mh(k) * at.plane + i]);
         b.nxt.H.rest[i] = hdec[LH::REST];
         b.nxt.LAM[i] = lam;
         b.nxt.PHI[i] = phin;
@@ -1074,7 +1074,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
         if (k == L::REST)
           b.nxt.G.rest[i] = gdec[k];
         else
-          b.nxt.G.mov[mg(k) * at.plane + i] = genc[k];
+          store_state<kStream>(genc[k], &b.nxt.G.mov[mg(k) * at.plane + i]);
       }
     }
     __syncthreads();  // the LDS tiles are refilled by the next tile
@@ -1085,9 +1085,16 @@ template <class Codec, class L, class LH, bool kGen>
 struct DevFused2D {
   template <int TY, bool kWalls>
   static int run(const Geo& g, const Coef<float>& K, const DevStep& b, hipStream_t st) {
+    if constexpr (TY >= 8)
+      if (streams_out((int64_t)(2 * ((L::Q + LH::Q - 2) * 2 + 16)) * g.N))
+        return run<TY, kWalls, true>(g, K, b, st);
+    return run<TY, kWalls, false>(g, K, b, st);
+  }
+  template <int TY, bool kWalls, bool kStream>
+  static int run(const Geo& g, const Coef<float>& K, const DevStep& b, hipStream_t st) {
     constexpr int TX = 64;
     constexpr int NT = TileShape<TX, TY>::NT;
-    auto kernel = k_dev_fused2d<TX, TY, Codec, L, LH, kGen, kWalls>;
+    auto kernel = k_dev_fused2d<TX, TY, Codec, L, LH, kGen, kWalls, kStream>;
     const int tiles_x = (g.nx + TX - 1) / TX;
     const int tiles_y = (g.ny + TY - 1) / TY;
     const int ntiles = tiles_x * tiles_y;

