@@ -931,7 +931,9 @@ struct AdjOps {
     });
     return check_launch(ctx, "adjoint seed");
   }
-  static int step(gplbm_ctx* ctx, const void* s0, const void* s1) {
+  // carried: c of state s1 was left in A4 by the step before; keep_c: leave that
+  // of s0 there for the next.
+  static int step(gplbm_ctx* ctx, const void* s0, const void* s1, bool carried, bool keep_c) {
     const Geo g = make_geo(ctx->p);
     const Coef<double> K = make_coef<double>(ctx->p);
     const int a = ctx->adj_cur, b = 1 - a;
@@ -942,10 +944,15 @@ struct AdjOps {
       using A = typename decltype(addr)::type;
       auto launch = [&](auto kgen) {
         constexpr bool G = decltype(kgen)::value;
-        hipLaunchKernelGGL((k_adj_ra<L, LH, FS, G, A>), gr, bl, 0, ctx->stream, g, K, lam_M_W2(ctx),
-                           S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
+        constexpr bool kHand = hands_c_on<A>();
+        if (kHand && carried)
+          hipLaunchKernelGGL((k_adj_ra<L, LH, FS, G, kHand, A>), gr, bl, 0, ctx->stream, g, K,
+                             lam_M_W2(ctx), S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
+        else
+          hipLaunchKernelGGL((k_adj_ra<L, LH, FS, G, false, A>), gr, bl, 0, ctx->stream, g, K,
+                             lam_M_W2(ctx), S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
         hipLaunchKernelGGL((k_adj_rb<L, LH, FS, G, A>), gr, bl, 0, ctx->stream, g, K, lam_M_W2(ctx),
-                           S0, S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj);
+                           S0, S1, ctx->adj.set[a], ctx->adj.set[b], ctx->adj, keep_c);
       };
       by_scheme<A>(gen, launch);
     });
@@ -1011,8 +1018,8 @@ struct AdjSeedFn {
 };
 template <class L, class LH, class FS>
 struct AdjStepFn {
-  static int run(gplbm_ctx* c, const void* a, const void* b) {
-    return AdjOps<L, LH, FS>::step(c, a, b);
+  static int run(gplbm_ctx* c, const void* a, const void* b, bool carried, bool keep_c) {
+    return AdjOps<L, LH, FS>::step(c, a, b, carried, keep_c);
   }
 };
 template <class L, class LH, class FS>
@@ -1085,9 +1092,13 @@ int gplbm_adjoint_segment(gplbm_ctx* ctx, const void* states, uint64_t stride, i
   uint64_t need = 0;
   if (gplbm_checkpoint_bytes(&ctx->p, &need) || stride < need) return GPLBM_E_INVALID;
   if (!ctx->adj_ready) return fail(ctx, GPLBM_E_STATE, "adjoint segment before adjoint begin");
+  if (int rc = use_device(ctx)) return rc;
   const char* s = (const char*)states;
+  // a step hands the c of the state it shares with the next one on
   for (int64_t j = n - 1; j >= 0; --j)
-    if (int rc = gplbm_adjoint_step(ctx, s + j * stride, s + (j + 1) * stride)) return rc;
+    if (int rc = adj_dispatch<AdjStepFn>(ctx, (const void*)(s + j * stride),
+                                         (const void*)(s + (j + 1) * stride), j != n - 1, j != 0))
+      return rc;
   return GPLBM_OK;
 }
 
@@ -1095,7 +1106,7 @@ int gplbm_adjoint_step(gplbm_ctx* ctx, const void* state_n, const void* state_np
   if (!ctx || !state_n || !state_np1) return GPLBM_E_INVALID;
   if (!ctx->adj_ready) return fail(ctx, GPLBM_E_STATE, "adjoint step before adjoint begin");
   if (int rc = use_device(ctx)) return rc;
-  return adj_dispatch<AdjStepFn>(ctx, state_n, state_np1);
+  return adj_dispatch<AdjStepFn>(ctx, state_n, state_np1, false, false);
 }
 
 int gplbm_adjoint_finish(gplbm_ctx* ctx, const double* phi0, const double* c0, double* phi0_bar,

@@ -147,6 +147,28 @@ struct FwdLoads<L, LH, DevFwdState<Codec>> {
   }
 };
 
+// The same where c is known: between the steps of a segment on a periodic grid,
+// the second kernel of a reverse step n + 1 leaves the c^{n+1} that it summed
+// for the first kernel of step n, which then reads one value instead of pulling
+// LH::Q: 96^3 FP64 212 -> 197 us a step, FP32 178 -> 169, 256^3 FP64 3.77 ->
+// 3.55 ms, 512^2 FP64 33.4 -> 31.2 us.  With walls it lost (80^3
+// FP64 141 -> 146-151 us, 96^3 243 -> 250).
+template <class Addr>
+constexpr bool hands_c_on() {
+  return std::is_same<Addr, AddrPlane<false>>::value;
+}
+template <class L>
+struct FwdCarried {
+  Stencil<L, double> st;
+  double c;
+  template <class S, class A>
+  __device__ FwdCarried(const S* phi, const double* cf, const A& a) : st(a, phi), c(cf[a.node()]) {}
+  template <class A>
+  __device__ NodeFwd<L> eval(const Coef<double>& K, const A&) const {
+    return node_fwd_from<L>(K, c, st(0, 0, 0), st);
+  }
+};
+
 // Derivatives of the closure mu(c, phi): 1 and c_s - c_l for equal
 // curvatures; for general quadratic free energies, with
 // mu = fac (c - phi m_l - (1 - phi) m_s), fac = E / (eps_s phi + eps_l (1 - phi)):
@@ -318,18 +340,24 @@ __device__ __forceinline__ double gather_Gb(const AdjSet& P, int k, const A& a) 
 // The two halves of a reverse step at one node (the two kernels below).
 //
 // reverse_g: the reverse of the g collision of step n+1.  Writes the adjoint
-// of the node's pulled g~^{n+1} (C.A1), and returns the adjoint of grad phi^{n+1} with the previous step's B3 added (a2), of c^{n+1}
-// (a3), the local adjoint of phi^{n+1} with the previous step's B4 added (a4),
-// and the lambda adjoint (lb).  The h collision of step n+1 (previous reverse
+// of the node's pulled g~^{n+1} (C.A1), and returns the adjoint of grad
+// phi^{n+1} with the previous step's B3 added (a2), of c^{n+1} (a3), the local
+// adjoint of phi^{n+1} with the previous step's B4 added (a4), and the lambda
+// adjoint (lb).  The h collision of step n+1 (previous reverse
 // step) also used grad phi^{n+1} and phi^{n+1}: their adjoints are added here,
 // so that the second half applies the transposed stencil once.
-template <class L, class LH, class FS, class Addr>
+template <class L, class LH, class FS, bool kCarried, class Addr>
 __device__ __forceinline__ void reverse_g(const Geo& g, const Coef<double>& K, double lam_M_W2,
-                                          const FS& S1, const AdjSet& P, const AdjSet& C,
-                                          const Addr& ad, double (&a2)[3], double& a3,
-                                          double& a4, double& lb) {
+                                          const FS& S1, const double* c1, const AdjSet& P,
+                                          const AdjSet& C, const Addr& ad, double (&a2)[3],
+                                          double& a3, double& a4, double& lb) {
   const int64_t i = ad.node();
-  const FwdLoads<L, LH, FS> fwd(S1, ad);
+  const auto fwd = [&] {
+    if constexpr (kCarried)
+      return FwdCarried<L>(S1.PHI, c1, ad);
+    else
+      return FwdLoads<L, LH, FS>(S1, ad);
+  }();
   double a_in[L::Q];
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) a_in[k] = gather_Gb<L>(P, k, ad);
@@ -363,13 +391,13 @@ __device__ __forceinline__ void reverse_g(const Geo& g, const Coef<double>& K, d
 // reverse_h: the reverse of the h collision of step n and of phi^{n+1} =
 // sum g~^{n+1} + S^n / 2.  p1b: the adjoint of
 // phi^{n+1} at this node gathered so far (a4 and the transposed stencil of
-// a2).  Writes B1 .. B4 of the node into C and accumulates its parameter
-// adjoints.
+// a2).  Writes B1 .. B4 of the node into C, accumulates its parameter adjoints
+// and with keep_c leaves c^n in A4.
 template <class L, class LH, class FS, class Addr>
 __device__ __forceinline__ void reverse_h(const Geo& g, const Coef<double>& K, double lam_M_W2,
                                           const FS& S0, const FS& S1, const AdjSet& P,
                                           const AdjSet& C, const AdjWork& w, const Addr& ad,
-                                          double p1b) {
+                                          double p1b, bool keep_c) {
   const int64_t i = ad.node();
   const FwdLoads<L, LH, FS> fwd(S0, ad);
   // total adjoint of h~*^n in this node's slots
@@ -446,11 +474,14 @@ __device__ __forceinline__ void reverse_h(const Geo& g, const Coef<double>& K, d
   C.B2[i] = p1b;
   for (int a = 0; a < 3; ++a) C.B3[a * g.N + i] = gb[a];
   C.B4[i] = phi_b;
+  if constexpr (hands_c_on<Addr>())
+    if (keep_c) w.A4[i] = f.c;  // its reader is this thread, above
   w.lamb[i] = lamb + lb;
   w.dlb[i] = dlb + dl_b;
 }
 
-template <class L, class LH, class FS, bool kGen, class Addr>
+// kCarried: A4 holds c^{n+1}, left there by k_adj_rb of the step before.
+template <class L, class LH, class FS, bool kGen, bool kCarried, class Addr>
 __global__ void __launch_bounds__(256) k_adj_ra(Geo g, Coef<double> Kin, double lam_M_W2,
                                                 FS S1, AdjSet P, AdjSet C, AdjWork w) {
   const Coef<double> K = variant<kGen>(Kin);
@@ -458,23 +489,25 @@ __global__ void __launch_bounds__(256) k_adj_ra(Geo g, Coef<double> Kin, double 
   if (!ad.inside()) return;
   const int64_t i = ad.node();
   double a2[3], a3, a4, lb;
-  reverse_g<L, LH>(g, K, lam_M_W2, S1, P, C, ad, a2, a3, a4, lb);
+  const double lamb = w.lamb[i];
+  reverse_g<L, LH, FS, kCarried>(g, K, lam_M_W2, S1, (const double*)w.A4, P, C, ad, a2, a3, a4, lb);
   for (int a = 0; a < L::D; ++a) w.A2[a * g.N + i] = a2[a];
   w.A3[i] = a3;
   w.A4[i] = a4;
-  w.lamb[i] += lb;
+  w.lamb[i] = lamb + lb;
 }
 
 template <class L, class LH, class FS, bool kGen, class Addr>
 __global__ void __launch_bounds__(256) k_adj_rb(Geo g, Coef<double> Kin, double lam_M_W2,
-                                                FS S0, FS S1, AdjSet P, AdjSet C, AdjWork w) {
+                                                FS S0, FS S1, AdjSet P, AdjSet C, AdjWork w,
+                                                bool keep_c) {
   const Coef<double> K = variant<kGen>(Kin);
   const Addr ad(g);
   if (!ad.inside()) return;
   const int64_t i = ad.node();
   // adjoint of phi^{n+1} at this node (A2, A4 hold both collisions' parts)
   const double p1b = w.A4[i] + stencil_adj_gather_at<L>(g, (const double*)w.A2, ad);
-  reverse_h<L, LH>(g, K, lam_M_W2, S0, S1, P, C, w, ad, p1b);
+  reverse_h<L, LH>(g, K, lam_M_W2, S0, S1, P, C, w, ad, p1b, keep_c);
 }
 
 // Seed: the adjoint of S_K from dJ/dphi^K and dJ/dc^K (c^K = sum of the
