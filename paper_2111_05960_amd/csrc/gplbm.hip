@@ -243,13 +243,24 @@ struct Tag {
 // Launch of a per-node kernel in the addressing that serves the grid: f(tag of
 // the policy, grid, block).
 template <class F>
-void by_addr(const gplbm_ctx* ctx, const F& f) {
+void by_addr(const gplbm_ctx* ctx, const F& f, bool dev_pair = false) {
   const gplbm_params& p = ctx->p;
   const int64_t plane = (int64_t)p.nx * p.ny;
-  // 32-bit byte offsets inside a plane of 8-byte values, z planes on the y
+  // 32-bit byte offsets inside a plane of 8-byte values, z planes on the z
   // axis of the grid
   if (plane < ((int64_t)1 << 29) && p.nz <= 65535) {
-    const dim3 grid((unsigned)((plane + 255) / 256), p.nz, 1), block(256, 1, 1);
+    // Bands of a plane by XCD, so that neighbouring rows and the lines that a
+    // shifted pull shares with its neighbour meet in one L2: where rows are
+    // short (16-bit codes: 250 x 230 x 190 with walls 744 -> 700 us a step,
+    // 200^3 522 -> 483, 512^3 with walls 8.68 -> 8.10 ms) and in 2-D (reverse
+    // step 512^2 FP64 31.2 -> 27.9 us, FP32 28.3 -> 24.7).  Not in 3-D FP64 and
+    // FP32, whose wider rows share little (100 x 90 x 70 FP64 112 -> 117 us,
+    // reverse step 80^3 with walls 143 -> 152), nor for a few blocks a plane
+    // (64^3 FP16 18.4 -> 18.9).
+    const int64_t nb = (plane + 255) / 256, rows = (nb + kNumXcd - 1) / kNumXcd;
+    const bool bands = (dev_pair || p.nz == 1) && nb >= 4 * kNumXcd && rows <= 65535;
+    const dim3 grid(bands ? kNumXcd : (unsigned)nb, bands ? (unsigned)rows : 1, p.nz),
+        block(256, 1, 1);
     if (p.bc[0] || p.bc[1] || p.bc[2])
       f(Tag<AddrPlane<true>>{}, grid, block);
     else
@@ -408,7 +419,7 @@ struct DevOps {
           using A = typename decltype(addr)::type;
           hipLaunchKernelGGL((k_dev_split_h<Codec, L, LH, A>), gr, bl, 0, ctx->stream, g, K, st);
           hipLaunchKernelGGL((k_dev_split_g<Codec, L, LH, A>), gr, bl, 0, ctx->stream, g, K, st);
-        });
+        }, true);
       }
       int rc = check_launch(ctx, "step");
       if (rc) return rc;
@@ -546,17 +557,17 @@ int choose_schedule(const gplbm_params& p) {
 // pair of kernels instead (the same bits).  A z-march takes at least four or
 // five planes of about 9 us however small the grid; the pair reads 1.5 times
 // the bytes, which costs little while they come from the last-level cache
-// (us per step, z-march / pair: 64^3 FP64 56 / 40, FP32 37 / 22, FP16 35 / 19;
-// 96^3 FP64 176 / 154, FP16 79 / 55; 128^3 FP32 162 / 180, FP16 131 / 133;
-// 200^3 FP16 624 / 520; 256^3 FP64 2350 / 2770, FP32 1170 / 1440, FP16 904 /
-// 982).  With walls the march's bounce bookkeeping moves the line up (256^3
-// FP32 1290 / 1430), and in the deviation formats the pair is the faster at
-// every size (256^3 FP16 1288 / 995, 512^3 9.5 / 9.0 ms).
+// (us per step, z-march / pair: 64^3 FP64 56 / 39, FP32 37 / 22, FP16 34 / 19;
+// 96^3 FP64 176 / 154, FP16 76 / 45; 128^3 FP32 162 / 177, FP16 128 / 124;
+// 200^3 FP16 622 / 485, 232^3 888 / 760; 256^3 FP64 2350 / 2840, FP32 1170 /
+// 1440, FP16 902 / 960).  With walls the march's bounce bookkeeping moves the
+// line up (256^3 FP32 1290 / 1430), and in the deviation formats the pair is
+// the faster at every size (256^3 FP16 1257 / 900, 512^3 9.1 / 8.1 ms).
 bool node_pair_faster(const gplbm_params& p) {
   if (two_d(p.lattice)) return false;
   const int64_t N = (int64_t)p.nx * p.ny * p.nz;
   const bool walls = p.bc[0] || p.bc[1] || p.bc[2];
-  if (p.precision >= GPLBM_FP16_DEV) return walls || N <= 10000000;
+  if (p.precision >= GPLBM_FP16_DEV) return walls || N <= 13000000;
   if (walls) return N <= 4000000;
   return N <= (p.precision == GPLBM_FP64 ? 2000000 : 1200000);
 }

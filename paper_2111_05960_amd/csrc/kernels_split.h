@@ -18,6 +18,7 @@
 
 #include "geometry.h"
 #include "node_math.h"
+#include "tiles.h"
 
 namespace gplbm {
 
@@ -33,7 +34,7 @@ struct StepBufs {
 
 // Addressing of the per-node kernels.  AddrGeneral takes any grid, by the
 // rules of geometry.h.  AddrPlane serves grids whose population planes are
-// shorter than 4 GiB: threads run over the nodes of a z plane (blockIdx.y), so
+// shorter than 4 GiB: threads run over the nodes of a z plane (blockIdx.z), so
 // a plane's base is a scalar and a neighbour a 32-bit offset wrapped once per
 // node, with no division or branch per population; with walls a bounced
 // population is a selected address.  Both give the same nodes.
@@ -95,13 +96,23 @@ struct AddrPlane {
   bool xm, xp, ym, yp, zm, zp;  // that neighbour lies beyond a wall
 
   __device__ AddrPlane(const Geo& g) : plane((int64_t)g.nx * g.ny) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t i = plane_block() * blockDim.x + threadIdx.x;
     in = i < (uint32_t)plane;
     const int yy = in ? i / (uint32_t)g.nx : 0;
-    set(g, in ? i - yy * g.nx : 0, yy, blockIdx.y);
+    set(g, in ? i - yy * g.nx : 0, yy, blockIdx.z);
   }
   __device__ AddrPlane(const Geo& g, int x_, int y_, int z_) : plane((int64_t)g.nx * g.ny), in(true) {
     set(g, x_, y_, z_);
+  }
+  // The block of 256 nodes of the plane that this block takes.  In bands
+  // (gridDim.y > 1, gridDim.x = kNumXcd, the XCD of a block by the round-robin
+  // order of dispatch) an XCD takes neighbouring blocks of the plane, and the
+  // same ones over four planes; then the bands turn, so that the XCDs of a
+  // plane's last, partly empty bands change.
+  static __device__ uint32_t plane_block() {
+    if (gridDim.y == 1) return blockIdx.x;
+    const uint32_t band = (blockIdx.x + (blockIdx.z >> 2)) % kNumXcd;
+    return band * gridDim.y + blockIdx.y;
   }
   __device__ void set(const Geo& g, int x_, int y_, int z_) {
     x = x_;
