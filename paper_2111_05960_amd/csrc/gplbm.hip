@@ -562,7 +562,7 @@ int choose_schedule(const gplbm_params& p) {
 // 200^3 FP16 622 / 485, 232^3 888 / 760; 256^3 FP64 2350 / 2840, FP32 1170 /
 // 1440, FP16 902 / 960).  With walls the march's bounce bookkeeping moves the
 // line up (256^3 FP32 1290 / 1430), and in the deviation formats the pair is
-// the faster at every size (256^3 FP16 1257 / 900, 512^3 9.1 / 8.1 ms).
+// the faster at every size (512^3 FP16 9.1 / 8.1 ms).
 bool node_pair_faster(const gplbm_params& p) {
   if (two_d(p.lattice)) return false;
   const int64_t N = (int64_t)p.nx * p.ny * p.nz;
