@@ -639,10 +639,25 @@ int finish_diagnostics(gplbm_ctx* ctx, const double* red, gplbm_diag* out) {
   return GPLBM_OK;
 }
 
+// Whether the n bytes at p lie in one allocation of the device's own memory.
+bool in_own_memory(const void* p, size_t n, int device) {
+  hipPointerAttribute_t attr{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&attr, p) != hipSuccess ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const size_t at = (size_t)((const char*)p - (const char*)base);
+  return attr.type == hipMemoryTypeDevice && attr.device == device && at <= size && n <= size - at;
+}
+
 // Copy of the context's current state to (save) or from a saved one: one
-// kernel where the saved state is memory of the context's own device at an
-// address that 16-byte vectors fit, else the runtime's copies, which also reach
-// other devices and host memory.
+// kernel where the whole saved state is memory of the context's own device at
+// an address that 16-byte vectors fit, else the runtime's copies, which also
+// reach other devices and host memory and refuse a size that reaches past the
+// saved state's allocation.
 int copy_state(gplbm_ctx* ctx, char* saved, bool save) {
   const int a = ctx->cur;
   char* const own[4] = {ctx->G[a], ctx->H[a], ctx->PHI[a], ctx->LAM[a]};
@@ -659,13 +674,8 @@ int copy_state(gplbm_ctx* ctx, char* saved, bool save) {
     at += bytes[j];
   }
   const uint64_t blocks = (total + kStreamThreads - 1) / kStreamThreads;
-  hipPointerAttribute_t attr{};
-  bool local = (uintptr_t)saved % 16 == 0 && blocks <= 0x7fffffffull;
-  if (local && hipPointerGetAttributes(&attr, saved) != hipSuccess) {
-    (void)hipGetLastError();
-    local = false;
-  }
-  if (local && attr.type == hipMemoryTypeDevice && attr.device == ctx->device) {
+  if ((uintptr_t)saved % 16 == 0 && blocks <= 0x7fffffffull &&
+      in_own_memory(saved, at, ctx->device)) {
     hipLaunchKernelGGL(k_copy_list, dim3((unsigned)blocks), dim3(kStreamThreads), 0, ctx->stream, c);
     return check_launch(ctx, what);
   }
