@@ -111,10 +111,10 @@ extern "C" {
 #define GPLBM_BF16_DEV 3
 
 /* kernel schedule */
-#define GPLBM_SCHED_AUTO 0  /* fused when the geometry allows it, else split; where the
-                               two kernels of the split schedule are the faster (small
-                               3-D grids, deviation formats with walls) a fused AUTO
-                               context steps with them: the same bits */
+#define GPLBM_SCHED_AUTO 0  /* fused when the geometry allows it and the two kernels of
+                               the split schedule are not the faster (as they are on
+                               small 3-D grids and in the deviation formats with walls),
+                               else split: the same bits */
 #define GPLBM_SCHED_SPLIT 1 /* two kernels per step */
 #define GPLBM_SCHED_FUSED 2 /* one kernel per step (tile halo recompute) */
 
@@ -282,7 +282,8 @@ int gplbm_adjoint_finish(gplbm_ctx* ctx, const double* phi0, const double* c0, d
  * that is not a multiple of 16. */
 int gplbm_stream_copy(const void* src, void* dst, uint64_t bytes, void* stream);
 
-/* Which schedule the context runs (GPLBM_SCHED_SPLIT or GPLBM_SCHED_FUSED). */
+/* Which schedule the context's steps run: GPLBM_SCHED_SPLIT (two kernels per
+ * step) or GPLBM_SCHED_FUSED (one), also for an AUTO context. */
 int gplbm_schedule(const gplbm_ctx* ctx);
 
 const char* gplbm_last_error(const gplbm_ctx* ctx);

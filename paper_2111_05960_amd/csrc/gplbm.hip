@@ -44,7 +44,6 @@ struct gplbm_ctx {
   int64_t step;
   bool ready;
   int sched;
-  bool node_steps;    // a fused context whose steps run as the per-node pair
   hipStream_t stream;
   int device;
   std::string err;
@@ -230,11 +229,6 @@ Geo make_geo(const gplbm_params& p) {
   return g;
 }
 
-// The context's steps run the fused kernel of its lattice.
-bool fused_steps(const gplbm_ctx* ctx) {
-  return ctx->sched == GPLBM_SCHED_FUSED && !ctx->node_steps;
-}
-
 template <class T>
 struct Tag {
   using type = T;
@@ -403,7 +397,7 @@ struct DevOps {
     for (int64_t n = 0; n < nsteps; ++n) {
       const int a = ctx->cur, b = 1 - a;
       const DevStep st{state(ctx, a), state(ctx, b)};
-      if (fused_steps(ctx)) {
+      if (ctx->sched == GPLBM_SCHED_FUSED) {
         // the general instantiation only for h^eq,alt or eps_s != eps_l
         const bool gen = ctx->p.h_scheme != GPLBM_H_SOURCE || ctx->p.free_energy != GPLBM_FE_EQUAL;
         int rc;
@@ -517,7 +511,8 @@ struct InitFn<A, void, void, void> {
 template <class L, class LH, class S, class C>
 struct StepFn {
   static int run(gplbm_ctx* c, int64_t n) {
-    return fused_steps(c) ? Ops<L, LH, S, C>::step_fused(c, n) : Ops<L, LH, S, C>::step_split(c, n);
+    return c->sched == GPLBM_SCHED_FUSED ? Ops<L, LH, S, C>::step_fused(c, n)
+                                         : Ops<L, LH, S, C>::step_split(c, n);
   }
 };
 template <class A>
@@ -543,18 +538,8 @@ struct DiagFn<A, void, void, void> {
   static int run(gplbm_ctx* c, double* r) { return A::diag(c, r); }
 };
 
-int choose_schedule(const gplbm_params& p) {
-  const bool fused_ok = p.precision >= GPLBM_FP16_DEV
-                            ? (two_d(p.lattice) || dev_fused_supported(p.nx, p.ny, p.nz, p.bc))
-                        : two_d(p.lattice)           ? fused2d_supported(p.nx, p.ny)
-                                                     : fused3d_supported(p.nx, p.ny, p.nz, p.bc);
-  if (p.schedule == GPLBM_SCHED_SPLIT) return GPLBM_SCHED_SPLIT;
-  if (p.schedule == GPLBM_SCHED_FUSED) return fused_ok ? GPLBM_SCHED_FUSED : -1;
-  return fused_ok ? GPLBM_SCHED_FUSED : GPLBM_SCHED_SPLIT;
-}
-
-// Whether the steps of an AUTO context on a fused 3-D grid run as the per-node
-// pair of kernels instead (the same bits).  A z-march takes at least four or
+// Whether the steps of an AUTO context on a 3-D grid run as the per-node pair
+// of kernels (the split schedule) instead of the z-march (the same bits).  A z-march takes at least four or
 // five planes of about 9 us however small the grid; the pair reads 1.5 times
 // the bytes, which costs little while they come from the last-level cache
 // (us per step, z-march / pair: 64^3 FP64 56 / 39, FP32 37 / 22, FP16 34 / 19;
@@ -570,6 +555,18 @@ bool node_pair_faster(const gplbm_params& p) {
   if (p.precision >= GPLBM_FP16_DEV) return walls || N <= 13000000;
   if (walls) return N <= 4000000;
   return N <= (p.precision == GPLBM_FP64 ? 2000000 : 1200000);
+}
+
+// The schedule that the context's steps run; -1 where a fused one is asked for
+// and the grid has none.
+int choose_schedule(const gplbm_params& p) {
+  const bool fused_ok = p.precision >= GPLBM_FP16_DEV
+                            ? (two_d(p.lattice) || dev_fused_supported(p.nx, p.ny, p.nz, p.bc))
+                        : two_d(p.lattice)           ? fused2d_supported(p.nx, p.ny)
+                                                     : fused3d_supported(p.nx, p.ny, p.nz, p.bc);
+  if (p.schedule == GPLBM_SCHED_SPLIT) return GPLBM_SCHED_SPLIT;
+  if (p.schedule == GPLBM_SCHED_FUSED) return fused_ok ? GPLBM_SCHED_FUSED : -1;
+  return fused_ok && !node_pair_faster(p) ? GPLBM_SCHED_FUSED : GPLBM_SCHED_SPLIT;
 }
 
 int use_device(gplbm_ctx* ctx) {
@@ -743,7 +740,6 @@ int gplbm_create(const gplbm_params* p, void* dev_buf, uint64_t bytes, void* str
   ctx->step = 0;
   ctx->ready = false;
   ctx->sched = sched;
-  ctx->node_steps = p->schedule == GPLBM_SCHED_AUTO && node_pair_faster(*p);
   ctx->stream = (hipStream_t)stream;
   if (hipGetDevice(&ctx->device) != hipSuccess) {
     delete ctx;
