@@ -242,7 +242,7 @@ void by_addr(const gplbm_ctx* ctx, const F& f, bool dev_pair = false) {
   const int64_t plane = (int64_t)p.nx * p.ny;
   // 32-bit byte offsets inside a plane of 8-byte values, z planes on the z
   // axis of the grid
-  if (plane < ((int64_t)1 << 29) && p.nz <= 65535) {
+  if (plane < ((int64_t)1 << 29) && p.nz <= kGridYZ) {
     // Bands of a plane by XCD, so that neighbouring rows and the lines that a
     // shifted pull shares with its neighbour meet in one L2: where rows are
     // short (16-bit codes: 250 x 230 x 190 with walls 744 -> 700 us a step,
@@ -251,21 +251,21 @@ void by_addr(const gplbm_ctx* ctx, const F& f, bool dev_pair = false) {
     // FP32, whose wider rows share little (100 x 90 x 70 FP64 112 -> 117 us,
     // reverse step 80^3 with walls 143 -> 152), nor for a few blocks a plane
     // (64^3 FP16 18.4 -> 18.9).
-    const int64_t nb = (plane + 255) / 256, rows = (nb + kNumXcd - 1) / kNumXcd;
-    const bool bands = (dev_pair || p.nz == 1) && nb >= 4 * kNumXcd && rows <= 65535;
+    const int64_t nb = (plane + kNodeThreads - 1) / kNodeThreads, rows = (nb + kNumXcd - 1) / kNumXcd;
+    const bool bands = (dev_pair || p.nz == 1) && nb >= 4 * kNumXcd && rows <= kGridYZ;
     const dim3 grid(bands ? kNumXcd : (unsigned)nb, bands ? (unsigned)rows : 1, p.nz),
-        block(256, 1, 1);
+        block(kNodeThreads, 1, 1);
     if (p.bc[0] || p.bc[1] || p.bc[2])
       f(Tag<AddrPlane<true>>{}, grid, block);
     else
       f(Tag<AddrPlane<false>>{}, grid, block);
   } else {
-    f(Tag<AddrGeneral>{}, dim3((p.nx + 63) / 64, (p.ny + 3) / 4, p.nz), dim3(64, 4, 1));
+    f(Tag<AddrGeneral>{}, general_grid(plane, p.nz), dim3(kNodeThreads, 1, 1));
   }
 }
 
-// f(general instantiation as a true / false type).  The addressing of the very
-// largest planes has only the general one, which reads the run's flags.
+// f(general instantiation as a true / false type).  The addressing of the grids
+// beyond AddrPlane has only the general one, which reads the run's flags.
 template <class A, class F>
 void by_scheme(bool gen, const F& f) {
   if constexpr (std::is_same_v<A, AddrGeneral>)
@@ -366,10 +366,6 @@ struct Ops {
 // the fused schedules are the 3-D z-march and the 2-D tile kernel).
 template <class Codec, class L, class LH>
 struct DevOps {
-  static dim3 block() { return dim3(64, 4, 1); }
-  static dim3 grid(const gplbm_ctx* ctx) {
-    return dim3((ctx->p.nx + 63) / 64, (ctx->p.ny + 3) / 4, ctx->p.nz);
-  }
   static DevState state(const gplbm_ctx* ctx, int a) {
     DevState s;
     s.G.mov = (uint16_t*)ctx->G[a];
@@ -384,7 +380,9 @@ struct DevOps {
     const Geo g = make_geo(ctx->p);
     const Coef<float> K = make_coef<float>(ctx->p);
     const DevState s = state(ctx, ctx->cur);
-    hipLaunchKernelGGL(k_dev_init_fields, grid(ctx), block(), 0, ctx->stream, g, K, phi0, c0, s);
+    const int64_t nb = (g.N + kNodeThreads - 1) / kNodeThreads;
+    hipLaunchKernelGGL(k_dev_init_fields, dim3((unsigned)(nb < kGridX ? nb : kGridX)),
+                       dim3(kNodeThreads), 0, ctx->stream, g, K, phi0, c0, s);
     by_addr(ctx, [&](auto addr, dim3 gr, dim3 bl) {
       hipLaunchKernelGGL((k_dev_init<Codec, L, LH, typename decltype(addr)::type>), gr, bl, 0,
                          ctx->stream, g, K, c0, s);

@@ -172,15 +172,13 @@ __global__ void __launch_bounds__(256) k_dev_init_fields(Geo g, Coef<float> K,
                                                          const double* __restrict__ phi0,
                                                          const double* __restrict__ c0,
                                                          DevState s) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= g.nx || y >= g.ny) return;
-  const int64_t i = node_index(g, x, y, z);
-  const float phi = float(phi0[i]);
-  const float mu0 = float(closure(K.q, c0[i], double(phi)));
-  s.PHI[i] = phi;
-  s.LAM[i] = h_lambda<float>(K, phi, mu0);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.N;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const float phi = float(phi0[i]);
+    const float mu0 = float(closure(K.q, c0[i], double(phi)));
+    s.PHI[i] = phi;
+    s.LAM[i] = h_lambda<float>(K, phi, mu0);
+  }
 }
 
 // (Addressed as in the step: 250x230x190 with walls 726 -> 443 us, 512^3 8.5 ->

@@ -33,19 +33,47 @@ struct StepBufs {
 };
 
 // Addressing of the per-node kernels.  AddrGeneral takes any grid, by the
-// rules of geometry.h.  AddrPlane serves grids whose population planes are
-// shorter than 4 GiB: threads run over the nodes of a z plane (blockIdx.z), so
-// a plane's base is a scalar and a neighbour a 32-bit offset wrapped once per
-// node, with no division or branch per population; with walls a bounced
-// population is a selected address.  Both give the same nodes.
+// rules of geometry.h.  AddrPlane serves grids of up to kGridYZ planes whose
+// population planes are shorter than 4 GiB: threads run over the nodes of a z
+// plane (blockIdx.z), so a plane's base is a scalar and a neighbour a 32-bit
+// offset wrapped once per node, with no division or branch per population; with
+// walls a bounced population is a selected address.  Both give the same nodes.
+constexpr int kNodeThreads = 256;
+constexpr int kGridYZ = 65535;          // blocks of a launch along y and z
+constexpr int64_t kGridX = 1 << 22;     // and along x (2^32 threads at most)
+
+// The launch of AddrGeneral: blocks over the nodes of a plane along x, in runs
+// of kGridX, planes along z, and along y the runs of a plane times the layers of
+// kGridYZ planes.
+__host__ __device__ inline int64_t general_runs(int64_t plane) {
+  const int64_t per_run = kGridX * kNodeThreads;
+  return (plane + per_run - 1) / per_run;
+}
+inline dim3 general_grid(int64_t plane, int nz) {
+  const int64_t nb = (plane + kNodeThreads - 1) / kNodeThreads;
+  const int64_t layers = ((int64_t)nz + kGridYZ - 1) / kGridYZ;
+  return dim3((unsigned)(nb < kGridX ? nb : kGridX), (unsigned)(general_runs(plane) * layers),
+              nz < kGridYZ ? nz : kGridYZ);
+}
+
 struct AddrGeneral {
   const Geo& g;
+  bool in;
   int x, y, z;
-  __device__ AddrGeneral(const Geo& g_)
-      : g(g_), x(blockIdx.x * blockDim.x + threadIdx.x), y(blockIdx.y * blockDim.y + threadIdx.y),
-        z(blockIdx.z) {}
-  __device__ AddrGeneral(const Geo& g_, int x_, int y_, int z_) : g(g_), x(x_), y(y_), z(z_) {}
-  __device__ bool inside() const { return x < g.nx && y < g.ny; }
+  __device__ AddrGeneral(const Geo& g_) : g(g_) {
+    const int64_t plane = (int64_t)g.nx * g.ny;
+    const int runs = int(general_runs(plane));
+    const int64_t i =
+        ((int64_t)(blockIdx.y % runs) * kGridX + blockIdx.x) * kNodeThreads + threadIdx.x;
+    const int64_t zz = (int64_t)(blockIdx.y / runs) * kGridYZ + blockIdx.z;
+    in = i < plane && zz < g.nz;
+    y = in ? int(i / g.nx) : 0;
+    x = in ? int(i - (int64_t)y * g.nx) : 0;
+    z = in ? int(zz) : 0;
+  }
+  __device__ AddrGeneral(const Geo& g_, int x_, int y_, int z_)
+      : g(g_), in(true), x(x_), y(y_), z(z_) {}
+  __device__ bool inside() const { return in; }
   __device__ int64_t node() const { return node_index(g, x, y, z); }
   // element of plane m among the q planes per z of a distribution
   __device__ int64_t slot(int m, int q) const {
