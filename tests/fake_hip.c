@@ -67,11 +67,13 @@ int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, void** st) {
   return 0;
 }
 int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t shared, void* st) {
-  (void)args, (void)shared, (void)st;
+  (void)shared, (void)st;
   const char* name = "?";
   for (int j = 0; j < nfun; ++j)
     if (fun[j] == f) name = fun_name[j];
-  note("launch %s %u %u %u %u %u %u\n", name, g.x, g.y, g.z, b.x, b.y, b.z);
+  /* the z-marching kernels' last argument: the planes of a chunk */
+  const int zc = strstr(name, "fused3d") ? *(const int*)args[6] : 0;
+  note("launch %s %u %u %u %u %u %u %d\n", name, g.x, g.y, g.z, b.x, b.y, b.z, zc);
   return 0;
 }
 int hipMemcpyAsync(void* dst, const void* src, size_t n, int kind, void* st) {

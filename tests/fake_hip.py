@@ -7,7 +7,7 @@ copy) and runs a script with these names:
   context(p, precision, schedule)   a context on 256-byte aligned "device" memory
   alloc(base, size, kind=2, device=0)   declare memory (2 device, 1 pinned host)
   log()    the launches and copies since the last log(): ("launch", kernel name,
-           grid, block) and ("copy", bytes)
+           grid, block, planes of a z-march's chunk) and ("copy", bytes)
 
 `out` is what the script returns (anything JSON can hold)."""
 from __future__ import annotations
@@ -57,7 +57,7 @@ def _main(lib: str):
         for line in fake.fake_log().decode().splitlines():
             w = line.split()
             out.append(["copy", int(w[1])] if w[0] == "copy" else
-                       ["launch", w[1], [int(v) for v in w[2:5]], [int(v) for v in w[5:8]]])
+                       ["launch", w[1], [int(v) for v in w[2:5]], [int(v) for v in w[5:8]], int(w[8])])
         fake.fake_clear()
         return out
 

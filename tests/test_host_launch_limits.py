@@ -32,7 +32,7 @@ for lat in LATTICES[dims]:
                 B.gplbm_adjoint_begin(ctx, 1 << 42, B.gplbm_adjoint_bytes(q), 0, 0)
                 B.gplbm_adjoint_step(ctx, 1 << 38, 1 << 39)
                 B.gplbm_adjoint_finish(ctx, 1 << 30, 1 << 31, 1 << 32, 1 << 33)
-                out += [[precision, schedule] + v[1:] for v in log() if v[0] == "launch"]
+                out += [[precision, schedule] + v[1:4] for v in log() if v[0] == "launch"]
                 B.gplbm_destroy(ctx)
 """
 
