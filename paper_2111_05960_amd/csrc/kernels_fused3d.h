@@ -89,8 +89,12 @@ __device__ __forceinline__ void bstore_nt(S v, __amdgpu_buffer_rsrc_t r, uint32_
 // plane group p - e_z and (x, y) - (e_x, e_y), whose byte offset inside a
 // population plane is xyb[1 - e_y][1 - e_x].  With walls bounced populations
 // (bits of `bounce` for the x and y walls, whole e_z layers at a z wall) are
-// the node's own opposite ones; a wavefront without any takes the plain pulls.
-template <class P, class S, bool kWalls>
+// the node's own opposite ones.  kPlainWaves: a wavefront without any takes
+// pulls of its own without the tests, which the forms that load ahead gain by
+// (FP32 256^3 with z walls 1263 us against 1299, 160^3 357 against 374); the
+// general FP64 form, which does not, is better off with one body (238^3 with
+// walls 2292 us against 2453, 317^3 5523 against 5850).
+template <class P, class S, bool kWalls, bool kPlainWaves>
 __device__ __forceinline__ void fetch(const S* base, int p, int nz, bool wz, int plane,
                                       const uint32_t (&xyb)[3][3], uint32_t bounce, S (&v)[P::Q]) {
   const int64_t groupB = int64_t(plane) * P::Q * sizeof(S);
@@ -106,7 +110,7 @@ __device__ __forceinline__ void fetch(const S* base, int p, int nz, bool wz, int
     uint32_t m = bounce;
     if (wz && p == 0) m |= ez_mask<P>(1);
     if (wz && p == nz - 1) m |= ez_mask<P>(-1);
-    if (__builtin_amdgcn_ballot_w64(m != 0u) != 0u) {
+    if (!kPlainWaves || __builtin_amdgcn_ballot_w64(m != 0u) != 0u) {
 #pragma unroll
       for (int k = 0; k < P::Q; ++k) {
         if ((m >> k) & 1u)
@@ -320,10 +324,10 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
     // pulls of plane p (h or g); a source beyond a wall gives the node's own
     // opposite population (bounce-back); a plane beyond a z wall is never read
     auto fetch_h = [&](int p, S (&v)[QH]) {
-      fetch<LH, S, kWalls>(b.H, p, nz, wz, plane, xyb, bmh, v);
+      fetch<LH, S, kWalls, kPrefetch>(b.H, p, nz, wz, plane, xyb, bmh, v);
     };
     auto fetch_g = [&](int p, S (&v)[Q]) {
-      fetch<L, S, kWalls>(b.G, p, nz, wz, plane, xyb, bmg, v);
+      fetch<L, S, kWalls, kPrefetch>(b.G, p, nz, wz, plane, xyb, bmg, v);
     };
     // first plane: the halo plane below the chunk, or the bottom plane at a
     // z wall
@@ -354,6 +358,10 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
       // past a top wall: no plane, only the completion of plane nz - 1
       const bool closing = wz && p == nz;
       const bool work = !kWalls || (active && !closing);
+      // whether plane p + 1 pulls; past a top wall none does (with walls a flat
+      // box would load a plane in six for nothing: 1000 x 1000 x 5 FP64 general
+      // 1030 us, 920 without)
+      const bool pulls_next = p < z1 && !(wz && p + 1 == nz);
       if constexpr (!kPrefetch) fetch_phi(p + 1, phi_next);
       put_phi(p + 1, phi_next);
       if constexpr (kPrefetch) {
@@ -365,12 +373,12 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
       const bool bz_up = wz && p == 0;
       const int sA = ring3(p);
       const bool own_p = p >= z0 && p < z1;
-      if constexpr (!kPrefetch) fetch_h(p, hv);
-      if constexpr (!kPrefetchG) fetch_g(p, gv);
 
       C hs[QH];
       double sg = 0.0;
       if (work) {
+        if constexpr (!kPrefetch) fetch_h(p, hv);
+        if constexpr (!kPrefetchG) fetch_g(p, gv);
         double c = 0.0;
 #pragma unroll
         for (int k = 0; k < QH; ++k) c = k == 0 ? double(hv[k]) : c + double(hv[k]);
@@ -414,7 +422,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
       // after the h stores: the wait for these pulls then waits for no store
       // issued later
       if constexpr (kPrefetch) {
-        if (p < z1) fetch_h(p + 1, hv);
+        if (pulls_next) fetch_h(p + 1, hv);
       }
 
       __syncthreads();
@@ -534,7 +542,7 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
         }
       }
       if constexpr (kPrefetchG) {
-        if (p < z1) fetch_g(p + 1, gv);
+        if (pulls_next) fetch_g(p + 1, gv);
       }
       sg_old = sg;
       if constexpr (kWalls) {
@@ -576,13 +584,16 @@ struct Fused3DWallConfig<D3Q19, LH, float> {
 };
 
 // The general instantiation in FP64 with h on D3Q19 needs the registers of 8
-// waves (64 x 5 tiles, g carried in registers: 512^3 20.6 and 21.0 ms with
-// general free energies and with h^eq,alt, against 21.3 in the form before and
-// 21.8 on the basic form's tiles), and with walls those of the prefetch.
+// waves (64 x 5 tiles, g carried in registers), and with walls those of the
+// prefetch too.  Periodic, h fetched ahead, in us against no prefetch and
+// against the basic form's tiles: 317^3 5020 (5500, 5900), 438 x 438 x 26 826
+// (910, 900), 256^3 2280 (2590, 2800).  With walls, without / with h fetched
+// ahead: 238^3 2290 / 2640.
+template <bool kWalls>
 struct Fused3DGeneralConfig {
   static constexpr int TX = 64, TY = 5, ZC = 32;
   static constexpr Carry carry = Carry::kRegisters;
-  static constexpr Prefetch prefetch = Prefetch::kNone;
+  static constexpr Prefetch prefetch = kWalls ? Prefetch::kNone : Prefetch::kH;
 };
 
 template <class L, class LH, class S, class C, bool kGen>
@@ -606,8 +617,8 @@ struct Fused3D {
   }
   static int launch(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {
     constexpr bool kGeneral = kGen && sizeof(S) == 8 && LH::Q == 19;
-    using Walls = std::conditional_t<kGeneral, Fused3DGeneralConfig, Fused3DWallConfig<L, LH, S>>;
-    using Periodic = std::conditional_t<kGeneral, Fused3DGeneralConfig, Fused3DConfig<L, LH, S>>;
+    using Walls = std::conditional_t<kGeneral, Fused3DGeneralConfig<true>, Fused3DWallConfig<L, LH, S>>;
+    using Periodic = std::conditional_t<kGeneral, Fused3DGeneralConfig<false>, Fused3DConfig<L, LH, S>>;
     if (g.bcx || g.bcy || g.bcz) return run<Walls, true>(g, K, b, st);
     return run<Periodic, false>(g, K, b, st);
   }
