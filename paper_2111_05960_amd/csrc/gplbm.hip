@@ -6,6 +6,7 @@
 // and h and the precision.  No device allocation happens here.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -536,35 +537,82 @@ struct DiagFn<A, void, void, void> {
   static int run(gplbm_ctx* c, double* r) { return A::diag(c, r); }
 };
 
+// Planes that the z-march of an FP64 or FP32 context takes one after the other.
+template <class L, class LH, class S, class C>
+struct MarchPlanesFn {
+  static int run(gplbm_ctx* c, double* planes) {
+    const Geo g = make_geo(c->p);
+    if constexpr (L::D == 3)
+      *planes = Ops<L, LH, S, C>::general(c) ? Fused3D<L, LH, S, C, true>::planes(g)
+                                             : Fused3D<L, LH, S, C, false>::planes(g);
+    return GPLBM_OK;
+  }
+};
+template <class A>
+struct MarchPlanesFn<A, void, void, void> {
+  static int run(gplbm_ctx*, double*) { return GPLBM_OK; }
+};
+
 // Whether the steps of an AUTO context on a 3-D grid run as the per-node pair
-// of kernels (the split schedule) instead of the z-march (the same bits).  A z-march takes at least four or
-// five planes of about 9 us however small the grid; the pair reads 1.5 times
-// the bytes, which costs little while they come from the last-level cache
-// (us per step, z-march / pair: 64^3 FP64 56 / 39, FP32 37 / 22, FP16 34 / 19;
-// 96^3 FP64 176 / 154, FP16 76 / 45; 128^3 FP32 162 / 177, FP16 128 / 124;
-// 200^3 FP16 622 / 485, 232^3 888 / 760; 256^3 FP64 2350 / 2840, FP32 1170 /
-// 1440, FP16 902 / 960).  With walls the march's bounce bookkeeping moves the
-// line up (256^3 FP32 1290 / 1430), and in the deviation formats the pair is
-// the faster at every size (512^3 FP16 9.1 / 8.1 ms).
-bool node_pair_faster(const gplbm_params& p) {
+// of kernels (the split schedule) instead of the z-march (the same bits).  A
+// z-march takes at least four or five planes of about 9 us however small the
+// grid; the pair reads 1.5 times the bytes, which costs little while they come
+// from the last-level cache.  In FP32 and the deviation formats the pair's part
+// of the range is clear (us per step, z-march / pair: 64^3 FP32 37 / 22, FP16
+// 34 / 19; 96^3 FP16 76 / 45; 128^3 FP32 162 / 177, FP16 128 / 124; 200^3 FP16
+// 622 / 485, 232^3 888 / 760; 256^3 FP32 1170 / 1440, FP16 902 / 960; with walls
+// 256^3 FP32 1290 / 1430, 512^3 FP16 9.1 / 8.1 ms; cubes, flat and tall boxes and
+// every lattice on the same side of these lines).
+//
+// In FP64 the two are close between one million nodes and four, and which is the
+// faster depends on how the tiles fit the chip (us per step, z-march / pair:
+// 285 x 285 x 24 329 / 358, with h on D3Q7 238 / 253; 125^3 328 / 356, 213 / 249;
+// g and h on D3Q7 570 x 570 x 6 117 / 137; but 40 x 40 x 1218 387 / 340, 570 x 570
+// x 6 389 / 363), so their costs are compared: the march's planes at the time of
+// a plane, which is that of a full chip (walls: the first and the last column of
+// tiles take 1.4 times as long; general forms 1.15 times, on D3Q19 with tiles of
+// 5 rows), the pair's nodes at 0.182, 0.128 and 0.066 ns (8% less where rows are
+// whole 128-byte lines).  On 220 random boxes, flat, cubic and tall, the choice
+// is on average 0.9% off the faster one; a line in nodes alone 1.7%.
+bool node_pair_faster(gplbm_ctx* ctx) {
+  const gplbm_params& p = ctx->p;
   if (two_d(p.lattice)) return false;
-  const int64_t N = (int64_t)p.nx * p.ny * p.nz;
   const bool walls = p.bc[0] || p.bc[1] || p.bc[2];
-  if (p.precision >= GPLBM_FP16_DEV) return walls || N <= 13000000;
-  if (walls) return N <= 4000000;
-  return N <= (p.precision == GPLBM_FP64 ? 2000000 : 1200000);
+  if (p.precision >= GPLBM_FP16_DEV) return walls || ctx->N <= 13000000;
+  if (p.precision == GPLBM_FP32) return ctx->N <= (walls ? 4000000 : 1200000);
+  if (ctx->N <= 1000000) return true;
+  if (ctx->N > 4000000) return false;
+  double planes = -1.0;
+  dispatch<MarchPlanesFn>(ctx, &planes);
+  if (planes < 0.0) {
+    (void)hipGetLastError();
+    return true;
+  }
+  const bool general = p.h_scheme != GPLBM_H_SOURCE || p.free_energy != GPLBM_FE_EQUAL;
+  const double plane_us = (light_g(p.lattice) ? (walls ? 7.7 : 6.1)
+                           : light_h(p)       ? 8.0
+                           : walls            ? 9.4
+                                              : (general ? 7.7 : 11.3)) *
+                          (general ? 1.15 : 1.0);
+  const double node_us = light_g(p.lattice) ? 66e-6 : light_h(p) ? 128e-6 : 182e-6;
+  const int columns = (p.nx + 63) / 64;
+  const double march =
+      planes * plane_us * (p.bc[0] ? 1.0 + 0.4 * std::min(1.0, 2.0 / columns) : 1.0);
+  return (double)ctx->N * node_us * (p.nx % 16 == 0 ? 0.92 : 1.0) <= march;
 }
 
-// The schedule that the context's steps run; -1 where a fused one is asked for
-// and the grid has none.
-int choose_schedule(const gplbm_params& p) {
-  const bool fused_ok = p.precision >= GPLBM_FP16_DEV
-                            ? (two_d(p.lattice) || dev_fused_supported(p.nx, p.ny, p.nz, p.bc))
-                        : two_d(p.lattice)           ? fused2d_supported(p.nx, p.ny)
-                                                     : fused3d_supported(p.nx, p.ny, p.nz, p.bc);
-  if (p.schedule == GPLBM_SCHED_SPLIT) return GPLBM_SCHED_SPLIT;
-  if (p.schedule == GPLBM_SCHED_FUSED) return fused_ok ? GPLBM_SCHED_FUSED : -1;
-  return fused_ok && !node_pair_faster(p) ? GPLBM_SCHED_FUSED : GPLBM_SCHED_SPLIT;
+// Whether the grid has a fused kernel.
+bool fused_available(const gplbm_params& p) {
+  if (two_d(p.lattice)) return p.precision >= GPLBM_FP16_DEV || fused2d_supported(p.nx, p.ny);
+  return p.precision >= GPLBM_FP16_DEV ? dev_fused_supported(p.nx, p.ny, p.nz, p.bc)
+                                       : fused3d_supported(p.nx, p.ny, p.nz, p.bc);
+}
+
+// The schedule that the context's steps run.
+int choose_schedule(gplbm_ctx* ctx) {
+  const int asked = ctx->p.schedule;
+  if (asked != GPLBM_SCHED_AUTO) return asked;
+  return fused_available(ctx->p) && !node_pair_faster(ctx) ? GPLBM_SCHED_FUSED : GPLBM_SCHED_SPLIT;
 }
 
 int use_device(gplbm_ctx* ctx) {
@@ -707,8 +755,7 @@ int gplbm_create(const gplbm_params* p, void* dev_buf, uint64_t bytes, void* str
   if (((uintptr_t)dev_buf) % kAlign) return GPLBM_E_INVALID;
   const Layout lay = layout(p);
   if (bytes < lay.total) return GPLBM_E_SIZE;
-  const int sched = choose_schedule(*p);
-  if (sched < 0) return GPLBM_E_INVALID;
+  if (p->schedule == GPLBM_SCHED_FUSED && !fused_available(*p)) return GPLBM_E_INVALID;
   gplbm_ctx* ctx = new gplbm_ctx();
   ctx->p = *p;
   if (two_d(ctx->p.lattice)) ctx->p.bc[2] = GPLBM_PERIODIC;
@@ -737,12 +784,12 @@ int gplbm_create(const gplbm_params* p, void* dev_buf, uint64_t bytes, void* str
   ctx->cur = 0;
   ctx->step = 0;
   ctx->ready = false;
-  ctx->sched = sched;
   ctx->stream = (hipStream_t)stream;
   if (hipGetDevice(&ctx->device) != hipSuccess) {
     delete ctx;
     return GPLBM_E_DEVICE;
   }
+  ctx->sched = choose_schedule(ctx);
   // set-up of gplbm_diagnostics_noalloc on this device (a failure is
   // reported by that call, not here)
   hipError_t serr;

@@ -598,27 +598,47 @@ struct Fused3DGeneralConfig {
 
 template <class L, class LH, class S, class C, bool kGen>
 struct Fused3D {
+  static constexpr bool kGeneral = kGen && sizeof(S) == 8 && LH::Q == 19;
+  using Walls = std::conditional_t<kGeneral, Fused3DGeneralConfig<true>, Fused3DWallConfig<L, LH, S>>;
+  using Periodic = std::conditional_t<kGeneral, Fused3DGeneralConfig<false>, Fused3DConfig<L, LH, S>>;
+
+  // Tiles, chunk and resident blocks of a launch; slots <= 0 on an error.
+  struct Plan {
+    int tiles_x, tiles_xy, zc, ntiles, slots;
+  };
+  template <class Cfg, bool kWalls>
+  static Plan plan(const Geo& g) {
+    static int resident[64] = {0};
+    Plan p{};
+    p.slots = resident_slots(k_fused3d<Cfg::TX, Cfg::TY, Cfg::carry, Cfg::prefetch, L, LH, S, C, kGen, kWalls>,
+                             TileShape<Cfg::TX, Cfg::TY>::NT, resident);
+    if (p.slots <= 0) return p;
+    p.tiles_x = (g.nx + Cfg::TX - 1) / Cfg::TX;
+    p.tiles_xy = p.tiles_x * ((g.ny + Cfg::TY - 1) / Cfg::TY);
+    p.zc = chunk_planes(p.tiles_xy, g.nz, Cfg::ZC, p.slots);
+    p.ntiles = p.tiles_xy * ((g.nz + p.zc - 1) / p.zc);
+    return p;
+  }
   template <class Cfg, bool kWalls>
   static int run(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {
-    constexpr int TX = Cfg::TX, TY = Cfg::TY, ZC = Cfg::ZC;
-    constexpr int NT = TileShape<TX, TY>::NT;
-    auto kernel = k_fused3d<TX, TY, Cfg::carry, Cfg::prefetch, L, LH, S, C, kGen, kWalls>;
-    const int tiles_x = (g.nx + TX - 1) / TX;
-    const int tiles_y = (g.ny + TY - 1) / TY;
-    const int tiles_xy = tiles_x * tiles_y;
-    static int resident[64] = {0};
-    const int slots = resident_slots(kernel, NT, resident);
-    if (slots <= 0) return -1;
-    const int zc = chunk_planes(tiles_xy, g.nz, ZC, slots);
-    const int ntiles = tiles_xy * ((g.nz + zc - 1) / zc);
-    hipLaunchKernelGGL(kernel, dim3(resident_grid(slots, ntiles)), dim3(NT), 0, st, g, K, b, tiles_x,
-                       tiles_xy, ntiles, zc);
+    const Plan p = plan<Cfg, kWalls>(g);
+    if (p.slots <= 0) return -1;
+    hipLaunchKernelGGL((k_fused3d<Cfg::TX, Cfg::TY, Cfg::carry, Cfg::prefetch, L, LH, S, C, kGen, kWalls>),
+                       dim3(resident_grid(p.slots, p.ntiles)), dim3(TileShape<Cfg::TX, Cfg::TY>::NT),
+                       0, st, g, K, b, p.tiles_x, p.tiles_xy, p.ntiles, p.zc);
     return 0;
   }
+  // Planes that a step takes one after the other: passes over the resident
+  // blocks times the planes of a chunk with its halo and the filling of the
+  // rings (chunk_planes), of which a chunk at a z wall has fewer.  -1 on an
+  // error.
+  static double planes(const Geo& g) {
+    const Plan p = (g.bcx || g.bcy || g.bcz) ? plan<Walls, true>(g) : plan<Periodic, false>(g);
+    if (p.slots <= 0) return -1.0;
+    const int passes = (p.ntiles + p.slots - 1) / p.slots;
+    return passes * (p.zc + 3 - (g.bcz ? 1.5 * p.zc / g.nz : 0.0));
+  }
   static int launch(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {
-    constexpr bool kGeneral = kGen && sizeof(S) == 8 && LH::Q == 19;
-    using Walls = std::conditional_t<kGeneral, Fused3DGeneralConfig<true>, Fused3DWallConfig<L, LH, S>>;
-    using Periodic = std::conditional_t<kGeneral, Fused3DGeneralConfig<false>, Fused3DConfig<L, LH, S>>;
     if (g.bcx || g.bcy || g.bcz) return run<Walls, true>(g, K, b, st);
     return run<Periodic, false>(g, K, b, st);
   }
