@@ -2,10 +2,13 @@
 the bit-equality tests, so that a change of a rule cannot leave a kernel of the
 fused schedules without a test (host side only, over the logging stand-in of the
 HIP runtime: one block per CU of 256)."""
+import re
+
 import pytest
 
 from tests import fake_hip
 from tests import test_gpu_long_marches as long_marches
+from tests import test_gpu_tile_heights as heights
 
 SCRIPT = """
 out = []
@@ -48,3 +51,29 @@ def test_long_marches_are_long(lib):
                                                       "Lb1ELb0EEEvNS_3GeoENS_4CoefIfEENS_7DevStepEiiii")):
             assert longest == 100, name
         assert any(zc < nz and nz % zc for zc, nz in lengths), name  # a ragged last chunk
+
+
+def _rows_and_store(name):
+    """rows of a tile, and whether the next state is stored past the caches"""
+    rows = int(re.search(r"fused2dILi64ELi(\d+)E", name).group(1))
+    gen, walls, past = re.search(r"Lb([01])ELb([01])ELb([01])EE", name).groups()
+    return rows, past == "1"
+
+
+def test_every_height_is_reached(lib):
+    want = {shape: rows for rows, shape in heights.HEIGHTS}
+    rows = _run(lib, heights.LATTICES, heights.WALLS, [(1,) + shape for shape in want])
+    for which, precision, walls, shape, name, grid, _ in rows:
+        fp64, other = want[tuple(shape[1:])]
+        assert _rows_and_store(name)[0] == (fp64 if precision == "fp64" else other), (shape, name)
+    assert {r for pair in want.values() for r in pair} == {1, 4, 8, 13}
+
+
+def test_both_stores_at_the_same_height(lib):
+    for (kind, which), cases in heights.LARGE.items():
+        for height, below, above in cases:
+            rows = _run(lib, {which: heights.LATTICES[which]}, heights.WALLS[:2],
+                        [(1, below, heights.NX), (1, above, heights.NX)])
+            for _, precision, walls, shape, name, grid, _ in rows:
+                if ("dev" if "dev" in precision else precision) == kind:
+                    assert _rows_and_store(name) == (height, shape[1] == above), (shape, name)
