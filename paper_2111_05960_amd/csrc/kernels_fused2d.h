@@ -96,7 +96,8 @@ struct Pull2D {
 // it (1024^2 4.3 TB/s, 2048^2 4.6 TB/s of algorithmic bytes).  Hence addresses
 // without divisions or branches, and every load of a tile in one batch before
 // the first barrier: 1024^2 FP64 85.2 -> 74.0 us, FP32 47.1 -> 30.0 us; 512^2
-// FP64 22.4 -> 17.4, FP32 15.1 -> 10.1 us; 512 x 8 with walls 10.5 -> 6.0 us.
+// FP64 22.4 -> 17.4, FP32 15.1 -> 10.1 us; 512 x 8 with walls 10.5 -> 5.3 us (6.0
+// on tiles of 8 rows).
 template <int TX, int TY, class L, class LH, class S, class C, bool kGen, bool kWalls, bool kStream>
 __global__ void __launch_bounds__((TileShape<TX, TY>::NT), (sizeof(S) == 4 ? 6 : 1))
     k_fused2d(Geo g, Coef<C> Kin, StepBufs<S> b, int tiles_x, int ntiles) {
@@ -244,7 +245,7 @@ inline bool fused2d_supported(int, int) { return true; }
 // blocks of 8 rows per CU, which 13 rows would not (FP32 512^2 10.1 and 14.6
 // us, FP16 10.5 and 14.6 us).
 inline int tile_rows(int nx, int ny, int tx, bool tall) {
-  constexpr int kCus = 256;
+  constexpr int kCus = 256;  // of an MI355X; on a part of one the choice is of another cost
   const int64_t columns = (nx + tx - 1) / tx;
   int best = 8;
   int64_t cost = INT64_MAX;
@@ -261,7 +262,9 @@ template <class L, class LH, class S, class C, bool kGen>
 struct Fused2D {
   template <int TY, bool kWalls>
   static int run(const Geo& g, const Coef<C>& K, const StepBufs<S>& b, hipStream_t st) {
-    // only grids of 8 rows and more are that large
+    // for the tiles of 8 rows and more that large grids take; strips of a few
+    // rows that are as large would gain 1-4% (300000 x 4 FP64 93 -> 89 us,
+    // 2000000 x 4 565 -> 558), which is not worth two more sets of kernels
     if constexpr (TY >= 8)
       if (streams_out((int64_t)(2 * (L::Q + LH::Q + 1)) * g.N * sizeof(S)))
         return run<TY, kWalls, true>(g, K, b, st);
