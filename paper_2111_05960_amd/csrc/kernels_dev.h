@@ -98,7 +98,9 @@ __device__ __forceinline__ uint16_t dev_encode(float v, float ref) {
 // The moving weights of every lattice are powers of two apart, so a tile may
 // hold the reference field times the smallest of them, w_min: the value of
 // population k is then w_k / w_min times a sum with that one operand, exactly
-// the sum with w_k ref.
+// the sum with w_k ref (while w_min ref is a normal number; below 1.2e-38 the
+// two may differ by a step of the subnormal numbers, 1.4e-45, which neither c
+// nor a 16-bit code of normal size holds).
 template <class L>
 constexpr double min_weight() {
   double w = 1.0;

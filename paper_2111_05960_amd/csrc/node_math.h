@@ -7,11 +7,41 @@
 // exact.  With these rules the FP64 path is reproducible to the last bit
 // from the formulas alone.
 //
+//   closure           mu = mu_eq + (c - (c_l phi + c_s (1 - phi)))
+//                     Eqs. (PotChim_Equilibirum), (Coexistence_Interpol);
+//                     general quadratic free energies, Eq. (Closure):
+//                     mu = (sqrt(eps_s eps_l) / (eps_s phi + eps_l (1 - phi)))
+//                          ((c - phi m_l) - (1 - phi) m_s)
+//   gradient          grad = (1/xi_s^2) sum_k w_k e_k d_k, d_k = (phi(x+e_k) - phi(x-e_k))/2
+//                     Eqs. (DerivDirec_Grad), (Grad); central differences on D2Q5 / D3Q7
+//   normal            n = grad / sqrt(|grad|^2 + eps_n^2)
+//   phi sources       G^st = kst S_phi, S_phi = 6 p(1-p) dc (mu - mu_eq), p = phi on [0, 1],
+//                     kst = -lambda M / W^2               Eqs. (SourceG_ST), (SourceTerm_Coexistence)
+//                     general: S_phi = 6 p(1-p) ((k2 mu^2 / 2 - (m_l - m_s) mu) - df_min),
+//                     k2 = (eps_l - eps_s) / sqrt(eps_l eps_s)   Eq. (SourceTerm)
+//                     G^ct_k = (4/W) phi(1-phi) e_k.n     Eq. (SourceG_CT)
+//                     G^dw = kdw 2 phi(1-phi)(1-2phi), kdw = -8 M / W^2   Eq. (SourceG_dw)
+//                     G_k = w_k (G^st + G^curv)           Eq. (TermG)
+//   g collision       g* = (g - omega_g ((g - w_k phi) + G_k/2)) + G_k
+//                     Eq. (LBE_PhaseField_Eq), omega_g = 1/(M / xi_s^2 + 1/2)
+//   h source          F = (mu (D_l - D_s)) grad + (a W dc) dphi/dt n,
+//                     H_k = (gamma w_k) e_k.F             Eq. (SourceTerm_LBE_h)
+//                     general: dc -> (ks mu + m_s) - m_l,
+//                     ks = -(eps_s - eps_l) / sqrt(eps_s eps_l)   Eq. (Anti-Trapping_Quadratic)
+//   h equilibrium     Lambda = (gamma D(phi)) mu, D = D_l q + D_s (1-q), q = phi on [0, 1]
+//                     h^eq_rest = c - (1 - w_rest) Lambda, h^eq_k = w_k Lambda
+//                     Eq. (Heq_Composition)
+//   h collision       h* = (h - omega_h ((h - h^eq_k) + H_k/2)) + H_k
+//                     Eq. (LBE_Composition), omega_h = 1/(1/(gamma xi_s^2) + 1/2)
+//   h alternative     h^eq,alt_k = w_k (Lambda + e_k.F / xi_s^2) (k moving),
+//                     h* = h - omega_h (h - h^eq,alt_k), no source
+//                     Eqs. (LBE_Concent_Alt), (Seq_Concent_Alt)
+//
 // The expressions are evaluated in forms that give the same bits with fewer
-// vector instructions: a product by a power of two is exact, so it goes into
-// the fused multiply-add of the sum that follows (one rounding, that of the
-// sum, either way), and what changes only its sign between a population and
-// its opposite is computed once.  A wave's FP32 addition or multiplication
+// vector instructions: a product by a power of two is exact (but for results
+// below the normal numbers), so it goes into the fused multiply-add of the sum
+// that follows (one rounding, that of the sum, either way), and what changes
+// only its sign between a population and its opposite is computed once.  A wave's FP32 addition or multiplication
 // occupies its SIMD for 2 cycles, a fused multiply-add for about 3 (4 with a
 // literal constant), a conversion and every FP64 operation for 4 (measured),
 // and a node of the FP16 z-march took 1390 instructions, now about 1040: 64^3
