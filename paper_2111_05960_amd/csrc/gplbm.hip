@@ -557,12 +557,17 @@ struct MarchPlanesFn<A, void, void, void> {
 // of kernels (the split schedule) instead of the z-march (the same bits).  A
 // z-march takes at least four or five planes of about 9 us however small the
 // grid; the pair reads 1.5 times the bytes, which costs little while they come
-// from the last-level cache.  In FP32 and the deviation formats the pair's part
-// of the range is clear (us per step, z-march / pair: 64^3 FP32 37 / 22, FP16
-// 34 / 19; 96^3 FP16 76 / 45; 128^3 FP32 162 / 177, FP16 128 / 124; 200^3 FP16
-// 622 / 485, 232^3 888 / 760; 256^3 FP32 1170 / 1440, FP16 902 / 960; with walls
-// 256^3 FP32 1290 / 1430, 512^3 FP16 9.1 / 8.1 ms; cubes, flat and tall boxes and
-// every lattice on the same side of these lines).
+// from the last-level cache (us per step, z-march / pair: 64^3 FP32 37 / 22,
+// FP16 34 / 19; 96^3 FP16 76 / 45; 128^3 FP32 162 / 177, FP16 128 / 124; 200^3
+// FP16 622 / 485, 232^3 888 / 760; 256^3 FP32 1170 / 1440, FP16 902 / 960; with
+// walls 256^3 FP32 1290 / 1430, 512^3 FP16 9.1 / 8.1 ms).  Rows that are not
+// whole lines, or half lines, cost the march more than the pair, and so do the
+// general forms, whose march is short of registers: with g and h on D3Q19 the
+// pair is then the faster at every size in the deviation formats (FP16 510 x 512
+// x 511 12.2 / 8.3 ms, 301^3 2.03 / 1.83, 1109 x 1109 x 26 2.72 / 2.21; general
+// 384^3 3.70 / 3.37, 512^3 8.3 / 8.0; but 480 x 512 x 511 7.37 / 7.51), and in
+// FP32 in the general form with walls (510 x 512 x 511 16.4 / 12.8, 500 x 500 x
+// 128 3.13 / 2.85; but 496 x 480 x 500 10.1 / 10.4).
 //
 // In FP64 the two are close between one million nodes and four, and which is the
 // faster depends on how the tiles fit the chip (us per step, z-march / pair:
@@ -578,8 +583,12 @@ bool node_pair_faster(gplbm_ctx* ctx) {
   const gplbm_params& p = ctx->p;
   if (two_d(p.lattice)) return false;
   const bool walls = p.bc[0] || p.bc[1] || p.bc[2];
-  if (p.precision >= GPLBM_FP16_DEV) return walls || ctx->N <= 13000000;
-  if (p.precision == GPLBM_FP32) return ctx->N <= (walls ? 4000000 : 1200000);
+  const bool general = p.h_scheme != GPLBM_H_SOURCE || p.free_energy != GPLBM_FE_EQUAL;
+  if (p.precision >= GPLBM_FP16_DEV)
+    return walls || ctx->N <= 13000000 || (!light_h(p) && (general || p.nx % 32));
+  if (p.precision == GPLBM_FP32)
+    return ctx->N <= (walls ? 4000000 : 1200000) ||
+           (!light_h(p) && general && walls && p.nx % 16);
   if (ctx->N <= 1000000) return true;
   if (ctx->N > 4000000) return false;
   double planes = -1.0;
@@ -588,7 +597,6 @@ bool node_pair_faster(gplbm_ctx* ctx) {
     (void)hipGetLastError();
     return true;
   }
-  const bool general = p.h_scheme != GPLBM_H_SOURCE || p.free_energy != GPLBM_FE_EQUAL;
   const double plane_us = (light_g(p.lattice) ? (walls ? 7.7 : 6.1)
                            : light_h(p)       ? 8.0
                            : walls            ? 9.4

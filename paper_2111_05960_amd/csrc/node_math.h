@@ -41,12 +41,12 @@
 // vector instructions: a product by a power of two is exact (but for results
 // below the normal numbers), so it goes into the fused multiply-add of the sum
 // that follows (one rounding, that of the sum, either way), and what changes
-// only its sign between a population and its opposite is computed once.  A wave's FP32 addition or multiplication
-// occupies its SIMD for 2 cycles, a fused multiply-add for about 3 (4 with a
-// literal constant), a conversion and every FP64 operation for 4 (measured),
-// and a node of the FP16 z-march took 1390 instructions, now about 1040: 64^3
-// FP16 38.0 -> 34.8 us per step, 512^3 FP16 with walls 10.08 -> 9.50 ms (with
-// the pulls batched), 512^2 FP32 10.2 -> 10.0 us.
+// only its sign between a population and its opposite is computed once.  A
+// wave's FP32 addition or multiplication occupies its SIMD for 2 cycles, a fused
+// multiply-add for about 3 (4 with a literal constant), a conversion and every
+// FP64 operation for 4 (measured), and a node of the FP16 z-march took 1390
+// instructions, now about 1040: 64^3 FP16 38.0 -> 34.8 us per step, 512^3 FP16
+// with walls 10.08 -> 9.50 ms (with the pulls batched), 512^2 FP32 10.2 -> 10.0.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -1,6 +1,6 @@
-"""AUTO takes the schedule that was measured to be the faster, on FP64 boxes
-where the two differ by more than 5% (us per step on MI355X, z-march and node
-pair).  Host side only, over the logging stand-in of the HIP runtime (one block
+"""AUTO takes the schedule that was measured to be the faster, on boxes where the
+two differ by more than 3% (us per step on MI355X, z-march and node pair; the
+FP64 ones in the basic scheme).  Host side only, over the logging stand-in of the HIP runtime (one block
 per CU of 256)."""
 import pytest
 
@@ -21,15 +21,31 @@ MEASURED = [
     ("gh", 1, (6, 570, 570), 125.5, 135.8), ("gh", 1, (6, 811, 811), 259.1, 277.1),
     ("gh", 1, (105, 105, 105), 88.6, 72.3), ("gh", 1, (1218, 40, 40), 182.0, 124.4),
 ]
+# precision, alternative h scheme, walls, (nz, ny, nx), on D3Q19
+MEASURED_NARROW = [
+    ("fp16dev", 0, 0, (256, 256, 256), 901, 964), ("fp16dev", 0, 0, (512, 512, 512), 6772, 7996),
+    ("fp16dev", 0, 0, (301, 301, 301), 2034, 1827), ("fp16dev", 0, 0, (26, 1109, 1109), 2721, 2210),
+    ("fp16dev", 0, 0, (26, 1088, 1088), 1819, 1876), ("bf16dev", 0, 0, (511, 512, 510), 12234, 8276),
+    ("fp16dev", 1, 0, (384, 384, 384), 3696, 3368), ("fp16dev", 1, 0, (512, 512, 512), 8339, 8010),
+    ("bf16dev", 0, 0, (26, 1109, 1109), 2790, 2191), ("fp16dev", 0, 1, (256, 256, 256), 1253, 939),
+    ("fp32", 0, 0, (60, 731, 731), 2944, 3235), ("fp32", 1, 1, (511, 512, 510), 16363, 12798),
+    ("fp32", 1, 1, (128, 500, 500), 3128, 2847), ("fp32", 1, 1, (384, 384, 384), 4742, 5040),
+    ("fp32", 1, 0, (60, 731, 731), 2947, 3272), ("fp32", 0, 0, (64, 64, 64), 37, 22),
+]
 SCRIPT = """
 LATTICES = {{"full": dict(lattice=wl.D3Q19), "h": dict(lattice=wl.D3Q19, h_lattice=1),
             "gh": dict(lattice=wl.D3Q7)}}
 out = [B.gplbm_schedule(context(wl.base_params(shape=shape, bc=(w, w, w), **LATTICES[which])))
        for which, w, shape, march, pair in {measured}]
+out += [B.gplbm_schedule(context(wl.base_params(lattice=wl.D3Q19, shape=shape, bc=(w, w, w),
+                                                h_scheme=alt), precision))
+        for precision, alt, w, shape, march, pair in {narrow}]
 """
 
 
 def test_auto_takes_the_faster(tmp_path):
-    told = fake_hip.run(fake_hip.build(tmp_path), SCRIPT.format(measured=MEASURED))
-    wrong = [(m, t) for m, t in zip(MEASURED, told) if t != (2 if m[3] < m[4] else 1)]
+    told = fake_hip.run(fake_hip.build(tmp_path),
+                        SCRIPT.format(measured=MEASURED, narrow=MEASURED_NARROW))
+    wrong = [(m, t) for m, t in zip(MEASURED + MEASURED_NARROW, told)
+             if t != (2 if m[-2] < m[-1] else 1)]
     assert not wrong
