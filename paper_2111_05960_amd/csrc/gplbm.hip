@@ -569,16 +569,15 @@ struct MarchPlanesFn<A, void, void, void> {
 // FP32 in the general form with walls (510 x 512 x 511 16.4 / 12.8, 500 x 500 x
 // 128 3.13 / 2.85; but 496 x 480 x 500 10.1 / 10.4).
 //
-// In FP64 the two are close between one million nodes and four, and which is the
-// faster depends on how the tiles fit the chip (us per step, z-march / pair:
-// 285 x 285 x 24 329 / 358, with h on D3Q7 238 / 253; 125^3 328 / 356, 213 / 249;
-// g and h on D3Q7 570 x 570 x 6 117 / 137; but 40 x 40 x 1218 387 / 340, 570 x 570
-// x 6 389 / 363), so their costs are compared: the march's planes at the time of
-// a plane, which is that of a full chip (walls: the first and the last column of
-// tiles take 1.4 times as long; general forms 1.15 times, on D3Q19 with tiles of
-// 5 rows), the pair's nodes at 0.182, 0.128 and 0.066 ns (8% less where rows are
-// whole 128-byte lines).  On 220 random boxes, flat, cubic and tall, the choice
-// is on average 0.9% off the faster one; a line in nodes alone 1.7%.
+// In FP64 the two are close between one million nodes and two (four with walls),
+// and which is the faster depends on how the tiles fit the chip (us per step,
+// z-march / pair: 285 x 285 x 24 329 / 358, with h on D3Q7 238 / 253; 125^3 328 /
+// 356, 213 / 249; g and h on D3Q7 with walls 405 x 405 x 24 230 / 269; but 40 x 40
+// x 1218 387 / 340, 570 x 570 x 6 389 / 363), so their costs are compared: the
+// march's planes at the time of a plane, which is that of a full chip (walls: the
+// first and the last column of tiles take 1.4 times as long; general forms 1.15
+// times, h on D3Q7 1.25, on D3Q19 with tiles of 5 rows), the pair's nodes at 0.182,
+// 0.128 and 0.066 ns (8% less where rows are whole 128-byte lines).
 bool node_pair_faster(gplbm_ctx* ctx) {
   const gplbm_params& p = ctx->p;
   if (two_d(p.lattice)) return false;
@@ -590,7 +589,7 @@ bool node_pair_faster(gplbm_ctx* ctx) {
     return ctx->N <= (walls ? 4000000 : 1200000) ||
            (!light_h(p) && general && walls && p.nx % 16);
   if (ctx->N <= 1000000) return true;
-  if (ctx->N > 4000000) return false;
+  if (ctx->N > (walls ? 4000000 : 2000000)) return false;
   double planes = -1.0;
   dispatch<MarchPlanesFn>(ctx, &planes);
   if (planes < 0.0) {
@@ -601,12 +600,12 @@ bool node_pair_faster(gplbm_ctx* ctx) {
                            : light_h(p)       ? 8.0
                            : walls            ? 9.4
                                               : (general ? 7.7 : 11.3)) *
-                          (general ? 1.15 : 1.0);
+                          (!general ? 1.0 : light_h(p) && !light_g(p.lattice) ? 1.25 : 1.15);
   const double node_us = light_g(p.lattice) ? 66e-6 : light_h(p) ? 128e-6 : 182e-6;
   const int columns = (p.nx + 63) / 64;
   const double march =
       planes * plane_us * (p.bc[0] ? 1.0 + 0.4 * std::min(1.0, 2.0 / columns) : 1.0);
-  return (double)ctx->N * node_us * (p.nx % 16 == 0 ? 0.92 : 1.0) <= march;
+  return (double)ctx->N * node_us * (p.nx % 16 == 0 ? 0.92 : 1.0) <= 1.02 * march;
 }
 
 // Whether the grid has a fused kernel.
