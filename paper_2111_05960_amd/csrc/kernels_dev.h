@@ -917,7 +917,9 @@ __global__ void __launch_bounds__((TileShape<TX, TY>::NT))
 // output rows per tile with walls: the wall bookkeeping (bounce masks,
 // mirror offsets, the third exchange buffer) does not fit the 128 VGPRs of
 // 16 waves per CU, so the walled z-march runs 64 x 9 tiles (12 waves, up to
-// 168 VGPRs) instead of spilling
+// 168 VGPRs: no spill in the basic form, 3 VGPRs in the general one on D3Q19).
+// Only an explicit request for the fused schedule takes it: AUTO steps walled
+// deviation runs by the node pair.
 #ifndef GPLBM_DEV_WALL_TY
 #define GPLBM_DEV_WALL_TY 9
 #endif

@@ -167,7 +167,8 @@ enum class Prefetch { kNone, kH, kBoth };
 // buffers by plane parity and h* pushed in ordered passes in FP64, else g
 // carried in registers, no prefetch of the pulls):
 //   D3Q19 FP64  18.5-19.0 against 19.8-20.1 (2.35 against 2.53); the LDS is
-//               full (163392 of 163840 bytes); a prefetch of h spills and one
+//               full (163392 of 163840 bytes) and so are the 168 VGPRs of 9
+//               waves, of which 8 spill; a prefetch of h spills more and one
 //               of both on 5 rows loses the neighbours' lines from the L2
 //               (21.0 and 21.9); chunks of at most 64 planes 18.8, 32 19.0, 128
 //               18.9
@@ -564,7 +565,7 @@ inline bool fused3d_supported(int nx, int ny, int nz, const int*) {
 
 // With zero-flux walls the e_z = +1 layer of the exchange is kept twice, so
 // D3Q19 carries g in registers: FP64 on 64 x 5 tiles (one 8-wave block per
-// CU; 512^3 20.5 ms against 20.6 without the prefetch, 256^3 2.45 against
+// CU, 4 of 256 VGPRs spilled; 512^3 20.5 ms against 20.6 without the prefetch, 256^3 2.45 against
 // 2.61; carry in the LDS 21.0, 2.56), FP32 on 64 x 9 (12 waves; 9.95 against
 // 11.0 ms, 1.29 against 1.38; 8 rows 10.4; carry in the LDS 10.4), in
 // 32-plane chunks.
