@@ -708,7 +708,7 @@ def main():
             if "vs_fp64" in r:
                 forms[name]["vs_fp64"] = r["vs_fp64"]
         # the same grid with zero-flux faces (the porous case's boundary in
-        # the paper): the walled instantiation of the z-march
+        # the paper): the walled z-march, or the node pair in the deviation format
         for prec in ("fp64", "fp32", "fp16dev"):
             name = form_name(prec) + "_walls"
             pw = dict(p, bc=(1, 1, 1))
