@@ -23,6 +23,9 @@ SOURCE = os.path.join(ROOT, "tests", "fake_hip.c")
 
 
 def build(folder) -> str:
+    from paper_2111_05960_amd import build as hipbuild
+    if not os.path.exists(hipbuild.LIB):
+        hipbuild.build()
     lib = os.path.join(str(folder), "libfakehip.so")
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", lib, SOURCE], check=True)
     return lib
